@@ -301,6 +301,20 @@ static int layer_forward_impl(const maskmoe_layer_desc* desc, const void* x, con
   // Training always takes the grouped-GEMM path, whose gate/up epilogue can keep the
   // pre-activations for the backward.
   const bool decode = uses_decode_path(d) && !train && !lora;
+  int pool = d.E;   // experts that the routing can select, and how evenly the prior weighs them
+  float skew = 1.0f;
+  if (d.route_mode == MASKMOE_ROUTE_HARD_MASK) {
+    pool = 0;
+    for (int i = 0; i < d.E; ++i) pool += mask[i] != 0;
+  } else if (d.route_mode == MASKMOE_ROUTE_SOFT_PRIOR) {
+    double s1 = 0.0, s2 = 0.0;
+    for (int i = 0; i < d.E; ++i) {
+      s1 += prior[i];
+      s2 += static_cast<double>(prior[i]) * prior[i];
+    }
+    skew = static_cast<float>(s1 * s1 / (s2 * d.E));
+  }
+  const int batch_rows = bf16 && !train && !lora ? maskmoe::batch_tile_rows(d.T, d.K, pool, skew) : 0;
   if (decode) {  // one workgroup routes every token and then permutes them
     e = maskmoe::launch_route_permute(x, w_router, d.T, d.d, d.E, d.K, d.route_mode, d.gate_mode, mask, prior, idx,
                                       gate, router_logits, d.n_shared, maskmoe::kGemmBM, pb, stream);
@@ -311,7 +325,7 @@ static int layer_forward_impl(const maskmoe_layer_desc* desc, const void* x, con
                               idx, gate, nullptr, router_logits, reinterpret_cast<float*>(ws + w.Z), stream);
     if (e != hipSuccess) return MASKMOE_E_HIP;
     maskmoe::record_mark(events, 1, stream);
-    e = maskmoe::launch_permute(idx, d.T, d.K, d.E, d.n_shared, maskmoe::kGemmBM, pb,
+    e = maskmoe::launch_permute(idx, d.T, d.K, d.E, d.n_shared, batch_rows ? batch_rows : maskmoe::kGemmBM, pb,
                                 reinterpret_cast<int32_t*>(ws + w.pcount), stream);
     if (e != hipSuccess) return MASKMOE_E_HIP;
   }
@@ -335,6 +349,10 @@ static int layer_forward_impl(const maskmoe_layer_desc* desc, const void* x, con
     e = maskmoe::launch_experts_bf16_decode(a, pb, reinterpret_cast<uint16_t*>(ws + w.H),
                                             reinterpret_cast<float*>(ws + w.P), reinterpret_cast<float*>(ws + w.O), y,
                                             stream, expert_marks);
+  } else if (batch_rows) {
+    e = maskmoe::launch_experts_batch(a, pb, batch_rows, pool, reinterpret_cast<uint16_t*>(ws + w.H),
+                                      reinterpret_cast<uint16_t*>(ws + w.O), reinterpret_cast<float*>(ws + w.TP), y,
+                                      stream, expert_marks);
   } else {
     const int64_t TK = static_cast<int64_t>(d.T) * d.K;
     const int64_t nonempty = TK < d.E ? TK : d.E;

@@ -1,0 +1,328 @@
+// Expert FFNs of a serving-sized batch (bf16): more tokens than the few-token kernels take, but
+// few enough rows per expert that the time is still the stream of the experts' weights from HBM.
+//
+// The 256 x 256 tiles of the many-token path (gemm_tile.hpp) keep about one k-tile of weights in
+// flight per CU behind a matrix pipeline that multiplies mostly padding there (4.1 TB/s). Here a
+// workgroup of four wavefronts owns 128 weight rows of one expert and BM token rows (64 or 128)
+// and streams 64-column chunks of both: chunks c + 1 and c + 2 travel in registers while chunk c
+// is multiplied from LDS on v_mfma_f32_32x32x16_bf16, so the 3 (BM 64) or 2 (BM 128) workgroups
+// of a CU keep 96 or 64 KB of weights in flight. Weight rows are the MFMA's row operand: a lane
+// then holds four neighbouring output columns of one token and stores them at once, and the gate
+// and up values of a column meet in one lane.
+// Workgroups that share weight rows (a group's row tiles) are neighbours on one XCD and read them
+// through its L2; weights that one workgroup alone reads are loaded non-temporally.
+// Measured, Mixtral-shaped layer, packed, soft prior: 17 tokens 671 -> 437 us (gate/up 271 us =
+// 6.9 TB/s), 96 tokens 663 -> 480 us, 300 tokens 664 -> 605 us; DeepSeek-shaped, 333 tokens:
+// gate/up 189 -> 145 us, down 131 -> 83 us. Three or four chunks in flight changed nothing, and
+// 256 token rows (one workgroup per CU) lost 15-60%: its loads, LDS accesses and products no
+// longer overlap.
+// The down projection splits its reduction when the tiles alone would leave the chip idle; its
+// fp32 slices are added, in order, by the combine.
+
+#include "common.hpp"
+#include "gemm_tile.hpp"
+#include "kernels.hpp"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace maskmoe {
+namespace {
+
+constexpr int kW = 128;           // weight rows per workgroup (one packed group)
+constexpr int kCK = kPackCols;    // reduction values per chunk
+// Byte offset of a token row that is not there: past any operand, so that the load returns zeros
+// without touching memory.
+constexpr uint32_t kNoRow = 0xf0000000u;
+
+struct BatchArgs {
+  const uint16_t* a;        // EPI 0: x [T, d] (rows via row_tok); EPI 1: H [rows, F]
+  const int32_t* row_tok;
+  const uint16_t* w;        // routed weights: EPI 0 [E, 2F, d], EPI 1 [E, d, F]
+  const uint16_t* ws;       // shared weights
+  const int32_t* offsets;   // [G+1]
+  const int32_t* tile_off;  // [G+1], tiles of BM rows
+  uint16_t* out;            // EPI 0: H [rows, F]; EPI 1: O [rows, d]
+  float* part;              // EPI 1 with split > 1: [split, rows, d] fp32
+  int G, E, N, K, F, rows;  // N: output columns (F or d), K: reduction length
+  int n_tiles, split, a_rows;   // a_rows: rows of a (T or rows)
+};
+
+constexpr int kThreads = 256, kRowsPerPiece = kThreads / 8;
+constexpr int kPW = kW / kRowsPerPiece;   // 16-byte pieces of weights per thread and chunk
+template <int BM>
+constexpr int kPieces = kPW + BM / kRowsPerPiece;
+
+// A raw buffer over [p, p + bytes), bytes < 2^32, p wave-uniform; reads past it return zeros.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint64_t u = static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32))) << 32 |
+                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a)));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(u), 0, static_cast<int>(bytes), 0x00020000);
+}
+
+// The stream of one tile: acc += W X^T over nc chunks. off[]: this thread's 16-byte pieces of a
+// chunk (the first PW are weights, in w from byte w0 + chunk * wstep; then tokens, in a from a0 + 128 chunk).
+// NT: non-temporal weight loads.
+template <int BM, bool NT>
+__device__ __forceinline__ void stream_tile(const void* w, uint32_t wbytes, uint32_t w0, uint32_t wstep,
+                                            const void* a, uint32_t abytes, uint32_t a0, int nc,
+                                            const uint32_t (&off)[kPieces<BM>], u32x4 (*lds)[(kW + BM) * 8], int wrow0,
+                                            int wrow1, int trow, f32x16 (&acc)[2][BM / 64]) {
+  constexpr int TN = BM / 64, PER = kPieces<BM>;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int dst = (tid >> 3) * 8 + ((tid & 7) ^ lds_swizzle(tid >> 3));   // piece i: + kThreads * i
+  const int sw = lds_swizzle(lane & 31);
+  u32x4 reg[2][PER];
+  // Past the last chunk the buffers are empty: the loads return zeros without touching memory,
+  // and every step has the same loads behind the ones its stores wait for.
+  constexpr int kNt = 2;   // the load's non-temporal bit
+  auto load = [&](int c, u32x4 (&r)[PER]) {
+    const __amdgpu_buffer_rsrc_t wr = make_rsrc(w, c < nc ? wbytes : 0), ar = make_rsrc(a, c < nc ? abytes : 0);
+    const uint32_t ws = w0 + static_cast<uint32_t>(c) * wstep, as = a0 + static_cast<uint32_t>(c) * (2 * kCK);
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      r[i] = i < kPW ? __builtin_amdgcn_raw_buffer_load_b128(wr, off[i], ws, NT ? kNt : 0)
+                    : __builtin_amdgcn_raw_buffer_load_b128(ar, off[i], as, 0);
+  };
+  auto store = [&](int buf, const u32x4 (&r)[PER]) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) lds[buf][dst + kThreads * i] = r[i];
+  };
+  auto compute = [&](int buf) {
+#pragma unroll
+    for (int kk = 0; kk < kCK / 16; ++kk) {
+      const int ch = (kk * 2 + (lane >> 5)) ^ sw;
+      const u32x4 w0 = lds[buf][wrow0 * 8 + ch], w1 = lds[buf][wrow1 * 8 + ch];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const u32x4 t = lds[buf][(trow + 32 * j) * 8 + ch];
+        acc[0][j] = mfma_32x32x16(w0, t, acc[0][j]);
+        acc[1][j] = mfma_32x32x16(w1, t, acc[1][j]);
+      }
+    }
+  };
+  // Chunk c sits in LDS buffer c & 1 and came from register set c & 1 (a compile-time index, so
+  // that the sets stay in registers), which takes chunk c + 2. The loads come first, the LDS
+  // stores of chunk c + 1 last. Returns whether another chunk follows.
+  int c = 0;
+  auto step = [&](auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    load(c + 2, reg[buf]);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(buf);
+    __builtin_amdgcn_sched_barrier(0);
+    store(buf ^ 1, reg[buf ^ 1]);
+    lds_sync();
+    return ++c < nc;
+  };
+  load(0, reg[0]);
+  load(1, reg[1]);
+  store(0, reg[0]);
+  lds_sync();
+  while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{})) {
+  }
+}
+
+// EPI 0: gate/up with SwiGLU; EPI 1: down. PACKED: weights in the packed layout.
+template <int EPI, int BM, bool PACKED>
+__global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void batch_gemm_kernel(const BatchArgs p) {
+  constexpr int TN = BM / 64;                  // 32-token fragments per wavefront
+  __shared__ u32x4 lds[2][(kW + BM) * 8];
+
+  const int per = p.n_tiles * p.split;         // jobs per row tile
+  const int live = p.tile_off[p.G] * per;
+  if (static_cast<int>(blockIdx.x) >= live) return;
+  const int lid = xcd_tile_id(live);
+  int lo = 0, hi = p.G;                        // tile_off[lo] <= lid / per < tile_off[hi]
+  const int mt = lid / per;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (p.tile_off[mid] <= mt) lo = mid; else hi = mid;
+  }
+  const int g = lo;
+  const int mtiles = p.tile_off[g + 1] - p.tile_off[g];
+  const int within = lid - p.tile_off[g] * per;
+  const int m = within % mtiles, nz = within / mtiles;
+  const int nt = nz / p.split, z = nz % p.split;
+  const int row0 = p.offsets[g] + m * BM, row_end = p.offsets[g + 1];
+  const int nc = p.K / kCK / p.split;          // chunks of this slice
+  const int c0 = z * nc;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;     // token part, weight half
+  const int n0 = nt * (EPI == 0 ? kW / 2 : kW);
+  const size_t mat = static_cast<size_t>(EPI == 0 ? 2 * p.F : p.N) * p.K;
+  const uint16_t* wg = g < p.E ? p.w + g * mat : p.ws + (g - p.E) * mat;
+  // byte offsets of chunk c0 within the expert's matrix (below 2^32: 2 F d < 2^31 elements)
+  const uint32_t w0 = PACKED ? 2u * (static_cast<uint32_t>(nt) * kW * p.K + static_cast<uint32_t>(c0) * kPackBlock)
+                             : 2u * static_cast<uint32_t>(c0) * kCK;
+  const uint32_t a0 = 2u * static_cast<uint32_t>(c0) * kCK;
+  const uint32_t wbytes = static_cast<uint32_t>(2 * mat), abytes = 2u * static_cast<uint32_t>(p.a_rows) * p.K;
+
+  // Piece i of this thread: row 32 i + tid / 8 of the stage (weight rows, then token rows), 16
+  // bytes at column chunk tid % 8. Weight rows past the end are clamped and token rows past it
+  // read as zeros: their products land in columns and rows that are never stored.
+  const int pr = tid >> 3, pc = tid & 7;
+  uint32_t off[kPieces<BM>];
+#pragma unroll
+  for (int i = 0; i < kPieces<BM>; ++i) {
+    if (i < kPW) {
+      const int r = kRowsPerPiece * i + pr;
+      int elem;
+      if (PACKED) elem = r * kPackCols;
+      else if (EPI == 0) elem = (r < kW / 2 ? n0 + r : p.F + n0 + r - kW / 2) * p.K;
+      else elem = min(n0 + r, p.N - 1) * p.K;
+      off[i] = static_cast<uint32_t>(elem + pc * 8) * 2u;
+    } else {
+      const int r = row0 + kRowsPerPiece * (i - kPW) + pr;
+      off[i] = r < row_end ? static_cast<uint32_t>((EPI == 0 ? p.row_tok[r] : r) * p.K + pc * 8) * 2u : kNoRow;
+    }
+  }
+  f32x16 acc[2][TN];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+  // fragment rows of the stage: weights (EPI 0: gate rows and the matching up rows), tokens
+  const int l32 = lane & 31;
+  const int wrow0 = (EPI == 0 ? wn * 32 : wn * 64) + l32, wrow1 = wrow0 + (EPI == 0 ? kW / 2 : 32);
+  const int trow = kW + wm * 32 * TN + l32;
+  constexpr int wstep = 2 * (PACKED ? kPackBlock : kCK);
+  if (mtiles == 1)
+    stream_tile<BM, true>(wg, wbytes, w0, wstep, p.a, abytes, a0, nc, off, lds, wrow0, wrow1, trow, acc);
+  else
+    stream_tile<BM, false>(wg, wbytes, w0, wstep, p.a, abytes, a0, nc, off, lds, wrow0, wrow1, trow, acc);
+
+  // acc[i][j][4 q + e]: weight row 8 q + 4 (lane >> 5) + e of fragment i, token row lane & 31 of
+  // fragment j
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int row = row0 + wm * 32 * TN + 32 * j + l32;
+    if (row >= row_end) continue;
+    if (EPI == 0) {
+      uint16_t* dsth = p.out + static_cast<size_t>(row) * p.F + n0 + wn * 32 + 4 * (lane >> 5);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float h[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = silu(acc[0][j][4 * q + e]) * acc[1][j][4 * q + e];
+        uint2 v;
+        v.x = f32x2_to_bf16x2(h[0], h[1]);
+        v.y = f32x2_to_bf16x2(h[2], h[3]);
+        *reinterpret_cast<uint2*>(dsth + 8 * q) = v;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int col = n0 + wn * 64 + 32 * i + 8 * q + 4 * (lane >> 5);
+          if (col >= p.N) continue;   // N % 64 == 0: four columns are all inside or all outside
+          const f32x16& a = acc[i][j];
+          if (p.split > 1) {
+            *reinterpret_cast<float4*>(p.part + (static_cast<size_t>(z) * p.rows + row) * p.N + col) =
+                make_float4(a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]);
+          } else {
+            uint2 v;
+            v.x = f32x2_to_bf16x2(a[4 * q], a[4 * q + 1]);
+            v.y = f32x2_to_bf16x2(a[4 * q + 2], a[4 * q + 3]);
+            *reinterpret_cast<uint2*>(p.out + static_cast<size_t>(row) * p.N + col) = v;
+          }
+        }
+    }
+  }
+}
+
+template <int EPI, int BM>
+void launch_bm(bool packed, int grid, const BatchArgs& p, hipStream_t s) {
+  if (packed) hipLaunchKernelGGL((batch_gemm_kernel<EPI, BM, true>), dim3(grid), dim3(kThreads), 0, s, p);
+  else hipLaunchKernelGGL((batch_gemm_kernel<EPI, BM, false>), dim3(grid), dim3(kThreads), 0, s, p);
+}
+
+template <int EPI>
+hipError_t launch(int bm, bool packed, int grid, const BatchArgs& p, hipStream_t s) {
+  if (bm == 64) launch_bm<EPI, 64>(packed, grid, p, s);
+  else launch_bm<EPI, 128>(packed, grid, p, s);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// By the rows an expert gets on average, since the time goes with the passes over the weights
+// (row tiles). Layer times with 64-row, 128-row and the many-token path's 256-row tiles:
+// Mixtral-shaped, plain routing, 30 rows 488 / 500 / 661 us, 64 rows 613 / 557 / 661, 100 rows
+// 718 / 608 / 674, 128 rows 837 / 788 / 682; hard mask over 4 experts, 30 rows 271 / 281 / 365,
+// 100 rows 377 / 337 / 366, 128 rows 434 / 427 / 366. A soft prior sends more rows to some
+// experts: `skew` is the share of them (1 / (E sum pi^2) with sum pi = 1) that a uniform
+// routing with the same concentration would use; soft prior over 4 of 8 experts, 91 rows on
+// that count 633 / 605 / 664, 106 rows 706 / 679 / 664. With dozens of experts the many-token
+// path's tiles are never full, and the line lies later: DeepSeek-shaped, soft, 112 rows
+// 396 / 354 / 399, 159 rows 483 / 424 / 409.
+int batch_tile_rows(int T, int K, int pool, float skew) {
+  if (T <= kDecodeMaxT) return 0;
+  const double avg = static_cast<double>(T) * K / pool;
+  if (avg <= 30) return 64;
+  return (pool >= 32 ? avg <= 112 : avg <= 104 * skew) ? 128 : 0;
+}
+
+// Slices of the down projection's reduction: up to about 600 workgroups, 16 chunks a slice.
+// (Mixtral-shaped: 256 workgroups in one slice leave a third of the resident slots empty; two
+// slices 480 us a layer at 96 tokens, four 490; at 300 tokens one slice 637, two 624, four 631.)
+constexpr int kDownTarget = 600;
+static int batch_split(int tiles, int rows, int d, int F) {
+  const int chunks = F / kCK;
+  int s = 1;
+  while (s < 8 && tiles * s * 2 <= kDownTarget && chunks % (2 * s) == 0 && chunks / (2 * s) >= 16 &&
+         static_cast<int64_t>(rows) * d * 4 * 2 * s <= static_cast<int64_t>(kTailPartBytes))
+    s *= 2;
+  return s;
+}
+
+hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int bm, int pool, uint16_t* H, uint16_t* O,
+                                float* part, void* y, hipStream_t stream, hipEvent_t* marks) {
+  const int64_t TK = static_cast<int64_t>(a.T) * a.K;
+  const int nonempty = static_cast<int>(std::min<int64_t>(TK, a.E));
+  const int shared_tiles = a.n_shared * ((a.T + bm - 1) / bm);
+  const int max_tiles = static_cast<int>(TK / bm) + nonempty + shared_tiles;
+  BatchArgs p{};
+  p.row_tok = pb.row_tok;
+  p.offsets = pb.offsets;
+  p.tile_off = pb.tile_off;
+  p.G = a.E + a.n_shared; p.E = a.E; p.F = a.F;
+  p.rows = a.T * (a.K + a.n_shared);
+
+  p.a = static_cast<const uint16_t*>(a.x);
+  p.w = static_cast<const uint16_t*>(a.w_gate_up);
+  p.ws = static_cast<const uint16_t*>(a.ws_gate_up);
+  p.out = H;
+  p.N = a.F; p.K = a.d; p.a_rows = a.T;
+  p.n_tiles = a.F / (kW / 2);
+  p.split = 1;
+  hipError_t err = launch<0>(bm, a.packed, max_tiles * p.n_tiles, p, stream);
+  if (err != hipSuccess) return err;
+  record_mark(marks, 0, stream);
+
+  p.a = H;
+  p.w = static_cast<const uint16_t*>(a.w_down);
+  p.ws = static_cast<const uint16_t*>(a.ws_down);
+  p.out = O;
+  p.part = part;
+  p.N = a.d; p.K = a.F; p.a_rows = p.rows;
+  p.n_tiles = (a.d + kW - 1) / kW;
+  const int active = static_cast<int>(std::min<int64_t>(pool, TK));
+  const int tiles = static_cast<int>(std::max<int64_t>(active, TK / bm)) + shared_tiles;   // about this many row tiles
+  p.split = batch_split(tiles * p.n_tiles, p.rows, a.d, a.F);
+  err = launch<1>(bm, a.packed, max_tiles * p.n_tiles * p.split, p, stream);
+  if (err != hipSuccess) return err;
+  record_mark(marks, 1, stream);
+  err = p.split > 1 ? launch_combine(a, pb, part, false, p.split, y, stream)
+                    : launch_combine(a, pb, O, true, 1, y, stream);
+  record_mark(marks, 2, stream);
+  return err;
+}
+
+}  // namespace maskmoe

@@ -882,6 +882,25 @@ static void launch_grouped(bool lora, bool packed, dim3 grid, const GemmArgs& g,
     hipLaunchKernelGGL((grouped_gemm_bf16<EPI>), grid, dim3(GEMM_THREADS), 0, stream, g);
 }
 
+hipError_t launch_combine(const ExpertArgs& a, const PermBuffers& pb, const void* O, bool ob, int split, void* y,
+                          hipStream_t stream) {
+  // bf16 O with K known: eight columns per thread
+  const dim3 cgrid = combine_grid(a.T, a.d), cgrid8 = combine_grid(a.T, a.d, kCombineColsOB), cblk(256);
+  if (!ob)
+    hipLaunchKernelGGL(combine_kernel<true>, cgrid, cblk, 0, stream, O, pb.inv, a.gate, a.T, a.K, a.n_shared, a.d, y,
+                       split, a.expert_out);
+  else if (a.K == 2)
+    hipLaunchKernelGGL((combine_kernel<true, 2, true>), cgrid8, cblk, 0, stream, O, pb.inv, a.gate, a.T, a.K,
+                       a.n_shared, a.d, y, 1, a.expert_out);
+  else if (a.K == 6)
+    hipLaunchKernelGGL((combine_kernel<true, 6, true>), cgrid8, cblk, 0, stream, O, pb.inv, a.gate, a.T, a.K,
+                       a.n_shared, a.d, y, 1, a.expert_out);
+  else
+    hipLaunchKernelGGL((combine_kernel<true, 0, true>), cgrid, cblk, 0, stream, O, pb.inv, a.gate, a.T, a.K,
+                       a.n_shared, a.d, y, 1, a.expert_out);
+  return hipGetLastError();
+}
+
 hipError_t launch_experts_bf16(const ExpertArgs& a, const PermBuffers& pb, uint16_t* H, float* O, float* part,
                                void* y, int max_tiles, hipStream_t stream, hipEvent_t* marks, uint16_t* ab,
                                const LoraArgs* lora) {
@@ -942,18 +961,7 @@ hipError_t launch_experts_bf16(const ExpertArgs& a, const PermBuffers& pb, uint1
   }
   record_mark(marks, 1, stream);
 
-  // O holds bf16 expert outputs; with K known, eight columns per thread
-  const dim3 cgrid = combine_grid(a.T, a.d), cgrid8 = combine_grid(a.T, a.d, kCombineColsOB), cblk(256);
-  if (a.K == 2)
-    hipLaunchKernelGGL((combine_kernel<true, 2, true>), cgrid8, cblk, 0, stream, O, pb.inv, a.gate, a.T, a.K,
-                       a.n_shared, a.d, y, 1, a.expert_out);
-  else if (a.K == 6)
-    hipLaunchKernelGGL((combine_kernel<true, 6, true>), cgrid8, cblk, 0, stream, O, pb.inv, a.gate, a.T, a.K,
-                       a.n_shared, a.d, y, 1, a.expert_out);
-  else
-    hipLaunchKernelGGL((combine_kernel<true, 0, true>), cgrid, cblk, 0, stream, O, pb.inv, a.gate, a.T, a.K,
-                       a.n_shared, a.d, y, 1, a.expert_out);
-  err = hipGetLastError();
+  err = launch_combine(a, pb, O, true, 1, y, stream);
   record_mark(marks, 2, stream);
   return err;
 }
@@ -1069,9 +1077,7 @@ hipError_t launch_experts_bf16_decode(const ExpertArgs& a, const PermBuffers& pb
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   record_mark(marks, 1, stream);
-  hipLaunchKernelGGL(combine_kernel<true>, combine_grid(a.T, a.d), dim3(256), 0, stream, O, pb.inv, a.gate, a.T, a.K,
-                     a.n_shared, a.d, y, p.split, a.expert_out);
-  err = hipGetLastError();
+  err = launch_combine(a, pb, O, false, p.split, y, stream);
   record_mark(marks, 2, stream);
   return err;
 }

@@ -143,6 +143,18 @@ int decode_split(int T, int d, int F, int E, int K, int n_shared);
 int decode_split_gate_up(int T, int d, int F, int E, int K, int n_shared);
 hipError_t launch_experts_bf16_decode(const ExpertArgs& a, const PermBuffers& pb, uint16_t* H, float* P, float* O,
                                       void* y, hipStream_t stream, hipEvent_t* marks);
+// bf16, a serving-sized batch (batch.hip): tokens above kDecodeMaxT but few enough rows per
+// expert that the weight stream bounds the layer. batch_tile_rows: the row-tile size to permute
+// and launch with, 0 when the many-token path is faster; pool: experts the routing can select,
+// skew: 1, or with a soft prior the smaller share of them that it concentrates on.
+// O: bf16 expert outputs [rows, d]; part: kTailPartBytes for the down projection's slices.
+int batch_tile_rows(int T, int K, int pool, float skew);
+hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int bm, int pool, uint16_t* H, uint16_t* O,
+                                float* part, void* y, hipStream_t stream, hipEvent_t* marks);
+// y = the gate-weighted combine of a bf16 layer's expert outputs: O [rows, d] bf16 (ob), or fp32
+// slices [split, rows, d].
+hipError_t launch_combine(const ExpertArgs& a, const PermBuffers& pb, const void* O, bool ob, int split, void* y,
+                          hipStream_t stream);
 // f32 path (no MFMA; fp32 end to end).
 hipError_t launch_experts_f32(const ExpertArgs& a, const PermBuffers& pb, float* H, float* O,
                               void* y, hipStream_t stream, hipEvent_t* marks);

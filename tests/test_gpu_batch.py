@@ -1,0 +1,45 @@
+"""The serving-batch expert kernels (more tokens than the few-token path takes, few rows per
+expert) against the oracle, at the edges of their tiles and of the rule that picks them: row
+groups of exactly one tile and one row more (64- and 128-row tiles; a shared expert's group
+holds every token), the last batch a rule takes and the first it leaves, d and F that are no
+multiple of a workgroup's 128 weight rows, one chunk of the reduction, and a split one. Bounds
+as in test_gpu_layer."""
+
+import pytest
+
+from paper_2609_34077_amd import _lib as L
+from paper_2609_34077_amd import synth
+from test_gpu_layer import check_layer
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(T, E, K, ns, d, F, mode=L.ROUTE_PLAIN, keep=None):
+    return synth.LayerConfig(f"batch_t{T}_e{E}_k{K}_s{ns}_d{d}_f{F}_m{mode}", T=T, d=d, F=F, E=E, K=K, n_shared=ns,
+                             route_mode=mode, gate_mode=L.GATE_P if ns else L.GATE_RENORM, mask_set=keep, seed=T + d)
+
+
+KEEP4 = (0, 2, 5, 7)
+CASES = [
+    _cfg(17, 8, 2, 0, 64, 64),                                        # the smallest batch; one chunk
+    _cfg(64, 8, 2, 1, 192, 320),                                      # 64-row tiles: one tile exactly
+    _cfg(65, 8, 2, 1, 256, 192),                                      # ... and one row more
+    _cfg(120, 8, 2, 0, 128, 2048, L.ROUTE_SOFT_PRIOR, KEEP4),         # 64-row tiles, split reduction
+    _cfg(121, 8, 2, 0, 128, 192, L.ROUTE_SOFT_PRIOR, KEEP4),          # 128-row tiles from here
+    _cfg(128, 8, 2, 1, 320, 128),                                     # one tile exactly
+    _cfg(129, 8, 2, 1, 128, 2048),                                    # one row more, split reduction
+    _cfg(208, 8, 2, 0, 256, 256, L.ROUTE_HARD_MASK, KEEP4),           # the last batch, four experts
+    _cfg(209, 8, 2, 0, 256, 256, L.ROUTE_HARD_MASK, KEEP4),           # the many-token path
+    _cfg(597, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),
+    _cfg(40, 256, 16, 8, 192, 64),                                    # the most experts and shared experts
+]
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
+def test_batch_rows(cfg):
+    check_layer(cfg)
+
+
+@pytest.mark.parametrize("cfg", [c for c in CASES if c.d % 128 == 0], ids=lambda c: c.name)
+def test_batch_packed(cfg):
+    check_layer(cfg, packed=True)
