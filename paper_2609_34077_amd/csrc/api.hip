@@ -325,7 +325,8 @@ static int layer_forward_impl(const maskmoe_layer_desc* desc, const void* x, con
                               idx, gate, nullptr, router_logits, reinterpret_cast<float*>(ws + w.Z), stream);
     if (e != hipSuccess) return MASKMOE_E_HIP;
     maskmoe::record_mark(events, 1, stream);
-    e = maskmoe::launch_permute(idx, d.T, d.K, d.E, d.n_shared, batch_rows ? batch_rows : maskmoe::kGemmBM, pb,
+    const int tile_rows = !bf16 ? maskmoe::kF32TileRows : batch_rows ? batch_rows : maskmoe::kGemmBM;
+    e = maskmoe::launch_permute(idx, d.T, d.K, d.E, d.n_shared, tile_rows, pb,
                                 reinterpret_cast<int32_t*>(ws + w.pcount), stream);
     if (e != hipSuccess) return MASKMOE_E_HIP;
   }

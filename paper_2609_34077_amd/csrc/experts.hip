@@ -20,8 +20,6 @@
 // kernels stream weight rows through LDS in cache-line-sized row segments (see the decode
 // section below); both projections split their reduction dimension when few experts are
 // active so that every CU keeps streaming. MFMA 16x16x32 with the token rows padded to 16.
-//
-// f32: plain fp32 loops (no MFMA), one thread per output element.
 
 #include <algorithm>
 #include <cmath>
@@ -798,62 +796,6 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_down_kernel(const DecodeAr
     }
 }
 
-// ------------------------------------------------------------------ f32 kernels
-
-__device__ __forceinline__ int group_of_row(const int32_t* offsets, int G, int pos) {
-  int lo = 0, hi = G;  // offsets[lo] <= pos < offsets[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (offsets[mid] <= pos) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-struct F32Args {
-  const float* x;
-  const int32_t* row_tok;
-  const int32_t* offsets;
-  const float* w_gate_up;
-  const float* w_down;
-  const float* ws_gate_up;
-  const float* ws_down;
-  float* H;
-  float* O;
-  int rows, d, F, E, G;
-};
-
-__global__ __launch_bounds__(256) void f32_gate_up_kernel(const F32Args p) {
-  const size_t id = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (id >= static_cast<size_t>(p.rows) * p.F) return;
-  const int pos = static_cast<int>(id / p.F), n = static_cast<int>(id % p.F);
-  const int g = group_of_row(p.offsets, p.G, pos);
-  const float* w = g < p.E ? p.w_gate_up + static_cast<size_t>(g) * 2 * p.F * p.d
-                           : p.ws_gate_up + static_cast<size_t>(g - p.E) * 2 * p.F * p.d;
-  const float* xr = p.x + static_cast<size_t>(p.row_tok[pos]) * p.d;
-  const float* wg = w + static_cast<size_t>(n) * p.d;
-  const float* wu = w + static_cast<size_t>(p.F + n) * p.d;
-  float a = 0.0f, b = 0.0f;
-  for (int k = 0; k < p.d; ++k) {
-    a = fmaf(xr[k], wg[k], a);
-    b = fmaf(xr[k], wu[k], b);
-  }
-  p.H[id] = (a / (1.0f + expf(-a))) * b;
-}
-
-__global__ __launch_bounds__(256) void f32_down_kernel(const F32Args p) {
-  const size_t id = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (id >= static_cast<size_t>(p.rows) * p.d) return;
-  const int pos = static_cast<int>(id / p.d), n = static_cast<int>(id % p.d);
-  const int g = group_of_row(p.offsets, p.G, pos);
-  const float* w = g < p.E ? p.w_down + static_cast<size_t>(g) * p.d * p.F
-                           : p.ws_down + static_cast<size_t>(g - p.E) * p.d * p.F;
-  const float* h = p.H + static_cast<size_t>(pos) * p.F;
-  const float* wr = w + static_cast<size_t>(n) * p.F;
-  float a = 0.0f;
-  for (int k = 0; k < p.F; ++k) a = fmaf(h[k], wr[k], a);
-  p.O[id] = a;
-}
-
 }  // namespace
 
 int device_cus_per_xcd() {
@@ -898,6 +840,12 @@ hipError_t launch_combine(const ExpertArgs& a, const PermBuffers& pb, const void
   else
     hipLaunchKernelGGL((combine_kernel<true, 0, true>), cgrid, cblk, 0, stream, O, pb.inv, a.gate, a.T, a.K,
                        a.n_shared, a.d, y, 1, a.expert_out);
+  return hipGetLastError();
+}
+
+hipError_t launch_combine_f32(const ExpertArgs& a, const PermBuffers& pb, const float* O, void* y, hipStream_t stream) {
+  hipLaunchKernelGGL(combine_kernel<false>, combine_grid(a.T, a.d), dim3(256), 0, stream, O, pb.inv, a.gate, a.T, a.K,
+                     a.n_shared, a.d, y, 1, a.expert_out);
   return hipGetLastError();
 }
 
@@ -1123,36 +1071,6 @@ hipError_t launch_pack_weights(const uint16_t* w_gate_up, const uint16_t* w_down
     return hipGetLastError();
   }
   return hipSuccess;
-}
-
-hipError_t launch_experts_f32(const ExpertArgs& a, const PermBuffers& pb, float* H, float* O,
-                              void* y, hipStream_t stream, hipEvent_t* marks) {
-  F32Args p;
-  p.x = static_cast<const float*>(a.x);
-  p.row_tok = pb.row_tok;
-  p.offsets = pb.offsets;
-  p.w_gate_up = static_cast<const float*>(a.w_gate_up);
-  p.w_down = static_cast<const float*>(a.w_down);
-  p.ws_gate_up = static_cast<const float*>(a.ws_gate_up);
-  p.ws_down = static_cast<const float*>(a.ws_down);
-  p.H = H;
-  p.O = O;
-  p.rows = a.T * (a.K + a.n_shared);
-  p.d = a.d; p.F = a.F; p.E = a.E; p.G = a.E + a.n_shared;
-  const size_t n1 = static_cast<size_t>(p.rows) * a.F, n2 = static_cast<size_t>(p.rows) * a.d;
-  hipLaunchKernelGGL(f32_gate_up_kernel, dim3((n1 + 255) / 256), dim3(256), 0, stream, p);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  record_mark(marks, 0, stream);
-  hipLaunchKernelGGL(f32_down_kernel, dim3((n2 + 255) / 256), dim3(256), 0, stream, p);
-  err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  record_mark(marks, 1, stream);
-  hipLaunchKernelGGL(combine_kernel<false>, combine_grid(a.T, a.d), dim3(256), 0, stream, O, pb.inv, a.gate, a.T,
-                     a.K, a.n_shared, a.d, y, 1, a.expert_out);
-  err = hipGetLastError();
-  record_mark(marks, 2, stream);
-  return err;
 }
 
 }  // namespace maskmoe

@@ -155,7 +155,10 @@ hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int 
 // slices [split, rows, d].
 hipError_t launch_combine(const ExpertArgs& a, const PermBuffers& pb, const void* O, bool ob, int split, void* y,
                           hipStream_t stream);
-// f32 path (no MFMA; fp32 end to end).
+// The combine of an fp32 layer: O [rows, d] fp32.
+hipError_t launch_combine_f32(const ExpertArgs& a, const PermBuffers& pb, const float* O, void* y, hipStream_t stream);
+// f32 path (f32.hip; fp32 end to end), the permutation in row tiles of kF32TileRows.
+constexpr int kF32TileRows = 32;
 hipError_t launch_experts_f32(const ExpertArgs& a, const PermBuffers& pb, float* H, float* O,
                               void* y, hipStream_t stream, hipEvent_t* marks);
 

@@ -830,29 +830,92 @@ __global__ __launch_bounds__(kRgThreads) void route_gemm_kernel(const RouteParam
   }
 }
 
-// fp32 router: plain fp32 dot products (no MFMA), one thread per (token, output).
-constexpr int kF32TT = 16;
-__global__ __launch_bounds__(256) void route_f32_kernel(const RouteParams p) {
-  __shared__ float logits[kF32TT * 256];
-  __shared__ float lo[256];
+// fp32 router: 16 tokens x up to 256 outputs (whole layers) per workgroup on
+// v_mfma_f32_16x16x4_f32, operands straight from memory, four k per lane and 16-byte load. With
+// up to four 16-wide output tiles the wavefronts split the reduction and their partial sums are
+// added in LDS in wavefront order; with more they split the tiles. (One thread per (token,
+// output) that walked its two rows alone took 30 us for 64 tokens, d 256, 8 experts.)
+constexpr int kF32TT = 16, kF32Waves = 4, kF32Outs = 256;
+
+// Four values of a row at k .. k + 3, zeros past d; VEC: d % 4 == 0 (16-byte loads).
+template <bool VEC>
+__device__ __forceinline__ f32x4 load_row4(const float* row, int k, int d) {
+  f32x4 r;
+  if (VEC) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(row + min(k, d - 4));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = k < d ? v[e] : 0.0f;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float v = row[min(k + e, d - 1)];
+      r[e] = k + e < d ? v : 0.0f;
+    }
+  }
+  return r;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(64 * kF32Waves) void route_f32_kernel(const RouteParams p) {
+  constexpr int NT = 64 * kF32Waves;
+  __shared__ float logits[kF32TT * kF32Outs];   // split reduction: [wavefront][16][64]
+  __shared__ float lo[kF32Outs];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, lg = lane >> 4;
   const int t0 = blockIdx.x * kF32TT;
   const int lg0 = blockIdx.y * p.lpw;
   const int nl = min(p.lpw, p.L - lg0);
-  const int nout = nl * p.E;
-  const float* x = static_cast<const float*>(p.x);
+  const int nout = nl * p.E, ntiles = (nout + 15) / 16;
   const float* w = static_cast<const float*>(p.w) + static_cast<size_t>(lg0) * p.E * p.d;
-  for (int i = threadIdx.x; i < kF32TT * nout; i += 256) {
-    const int tt = i / nout, o = i - tt * nout;
-    const int t = min(t0 + tt, p.T - 1);
-    const float* xr = x + static_cast<size_t>(t) * p.d;
-    const float* wr = w + static_cast<size_t>(o) * p.d;
-    float s = 0.0f;
-    for (int k = 0; k < p.d; ++k) s = fmaf(xr[k], wr[k], s);
-    logits[tt * 256 + o] = s;
+  const float* xr = static_cast<const float*>(p.x) + static_cast<size_t>(min(t0 + l16, p.T - 1)) * p.d;
+  for (int i = threadIdx.x; i < nout; i += NT) lo[i] = key_offset(p.mode, p.modep[lg0 * p.E + i]);
+  const int ksteps = (p.d + 15) / 16;
+  // acc += tokens x outputs 16 ot .. + 15 over k-steps [s0, s1): rows past the ends are clamped
+  auto tile = [&](int ot, int s0, int s1) {
+    const float* wr = w + static_cast<size_t>(min(16 * ot + l16, nout - 1)) * p.d;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    constexpr int U = 4;   // k-steps loaded together
+    for (int s = s0; s < s1; s += U) {
+      f32x4 a[U], b[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = s + u < s1 ? 16 * (s + u) + 4 * lg : p.d;   // zeros past the range
+        a[u] = load_row4<VEC>(xr, k, p.d);
+        b[u] = load_row4<VEC>(wr, k, p.d);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], b[u][e], acc, 0, 0, 0);
+    }
+    return acc;   // acc[i]: token 4 lg + i, output 16 ot + l16
+  };
+  int ld = kF32Outs;
+  if (ntiles <= 4) {
+    ld = 64;
+    const int per = (ksteps + kF32Waves - 1) / kF32Waves;
+    const int s0 = min(wave * per, ksteps), s1 = min(s0 + per, ksteps);
+    for (int ot = 0; ot < ntiles; ++ot) {
+      const f32x4 acc = tile(ot, s0, s1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) logits[(wave * kF32TT + 4 * lg + i) * 64 + 16 * ot + l16] = acc[i];
+    }
+    lds_sync();
+    for (int i = threadIdx.x; i < kF32TT * 64; i += NT) {
+      if ((i & 63) >= nout) continue;
+      float s = logits[i];
+#pragma unroll
+      for (int q = 1; q < kF32Waves; ++q) s += logits[q * kF32TT * 64 + i];
+      logits[i] = s;
+    }
+  } else {
+    for (int ot = wave; ot < ntiles; ot += kF32Waves) {
+      const f32x4 acc = tile(ot, 0, ksteps);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) logits[(4 * lg + i) * kF32Outs + 16 * ot + l16] = acc[i];
+    }
   }
-  for (int i = threadIdx.x; i < nout; i += 256) lo[i] = key_offset(p.mode, p.modep[lg0 * p.E + i]);
-  __syncthreads();
-  route_finalize(p, logits, 256, lo, t0, kF32TT, lg0, nl, 256);
+  lds_sync();
+  route_finalize(p, logits, ld, lo, t0, kF32TT, lg0, nl, NT);
 }
 
 template <int MB, int NB, int WN, int WK, bool FUSE = false, bool SPLIT = false>
@@ -907,10 +970,11 @@ hipError_t launch_route(bool bf16, const void* x, const void* w_router, int T, i
                 prior, idx, gate, margin, split ? zbuf : logits, esz);
     hipError_t err;
     if (!bf16) {
-      p.lpw = 256 / E < 1 ? 1 : 256 / E;
+      p.lpw = kF32Outs / E < 1 ? 1 : kF32Outs / E;
       if (p.lpw > p.L) p.lpw = p.L;
       dim3 grid((T + kF32TT - 1) / kF32TT, (p.L + p.lpw - 1) / p.lpw);
-      hipLaunchKernelGGL(route_f32_kernel, grid, dim3(256), 0, stream, p);
+      if (d % 4 == 0) hipLaunchKernelGGL(route_f32_kernel<true>, grid, dim3(64 * kF32Waves), 0, stream, p);
+      else hipLaunchKernelGGL(route_f32_kernel<false>, grid, dim3(64 * kF32Waves), 0, stream, p);
       err = hipGetLastError();
     } else if (T >= kRouteGemmMinT && d % kRgBK == 0 && p.L * E >= kRouteGemmMinOutputs) {
       p.lpw = kRgBN / E;
