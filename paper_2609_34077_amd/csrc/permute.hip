@@ -6,7 +6,8 @@
 //      expert (a prefix over chunks) and the group offsets, tile offsets and active list;
 //   3. permute_scatter_kernel: one workgroup per chunk places its entries, ranked among equal
 //      experts in entry order (ballots within a wavefront, per-wavefront counts in LDS).
-// Integer only, no global atomics: the result is the same as the single-workgroup version.
+// Up to kPermOneBlock entries take one workgroup instead (permute_one_kernel). Integer only, no
+// global atomics: the result is the same either way.
 
 #include "permute_block.hpp"
 
@@ -14,6 +15,7 @@ namespace maskmoe {
 namespace {
 
 constexpr int kPermThreads = 1024;   // one entry per thread and chunk
+constexpr int kPermOneBlock = 4 * kPermThreads;   // entries that one workgroup places alone
 
 __global__ __launch_bounds__(kPermThreads) void permute_count_kernel(const int32_t* __restrict__ idx, int n, int E,
                                                                     int32_t* __restrict__ counts) {
@@ -52,33 +54,7 @@ __global__ __launch_bounds__(kPermThreads) void permute_scan_kernel(int32_t* __r
     total[g] = run;
   }
   lds_sync();
-  if (tid < kWave) {   // one wavefront: lane l takes groups l*PG .. l*PG + PG - 1 in order
-    constexpr int PG = (kPermMaxGroups + kWave - 1) / kWave;
-    const int g0 = tid * PG;
-    int cnt[PG], til[PG], sc = 0, st = 0, sa = 0;
-#pragma unroll
-    for (int i = 0; i < PG; ++i) {
-      const int g = g0 + i;
-      cnt[i] = g < G ? (g < E ? total[g] : T) : 0;
-      til[i] = (cnt[i] + tile_rows - 1) / tile_rows;
-      sc += cnt[i];
-      st += til[i];
-      sa += cnt[i] > 0 ? 1 : 0;
-    }
-    int off = wave_inclusive_sum(sc) - sc, toff = wave_inclusive_sum(st) - st, na = wave_inclusive_sum(sa) - sa;
-#pragma unroll
-    for (int i = 0; i < PG; ++i) {
-      const int g = g0 + i;
-      if (g <= G) {   // offsets[G], tile_off[G]: the totals
-        pb.offsets[g] = off;
-        pb.tile_off[g] = toff;
-      }
-      if (g < G && cnt[i] > 0) pb.active[na++] = g;
-      off += cnt[i];
-      toff += til[i];
-    }
-    if (tid == kWave - 1) pb.n_active[0] = na;
-  }
+  if (tid < kWave) permute_scan_groups(total, T, E, n_shared, tile_rows, pb);
 }
 
 __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(const int32_t* __restrict__ idx, int T, int K,
@@ -93,12 +69,7 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(const int
   const int j = c * kPermChunk + tid;
   const int e = j < n ? idx[j] : -1;
   const bool valid = e >= 0 && e < E;
-  uint64_t same = __ballot(valid);   // lanes of this wavefront holding the same expert
-#pragma unroll
-  for (int b = 0; b < 9; ++b) {
-    const uint64_t bb = __ballot(valid && ((e >> b) & 1));
-    same &= ((e >> b) & 1) ? bb : ~bb;
-  }
+  const uint64_t same = same_expert(e, valid);
   for (int g = lane; g < E; g += kWave) wcnt[wave][g] = 0;
   lds_sync();
   const uint64_t lower = same & lanemask_lt(lane);
@@ -113,6 +84,14 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(const int
   }
 }
 
+// Up to IT * kPermThreads entries by one workgroup.
+template <int IT>
+__global__ __launch_bounds__(kPermThreads) void permute_one_kernel(const int32_t* __restrict__ idx, int T, int K, int E,
+                                                                  int n_shared, int tile_rows, PermBuffers pb) {
+  __shared__ PermLds s;
+  permute_block<IT>(idx, T, K, E, n_shared, tile_rows, pb, s, kPermThreads);
+}
+
 }  // namespace
 
 hipError_t launch_permute(const int32_t* idx, int T, int K, int E, int n_shared, int tile_rows,
@@ -120,6 +99,19 @@ hipError_t launch_permute(const int32_t* idx, int T, int K, int E, int n_shared,
   const int n = T * K;
   const int n_chunks = permute_chunks(T, K);
   if (n_chunks == 0) return hipSuccess;
+  // Few entries: one workgroup and one launch (a third of the launches; Mixtral-shaped layer, 17
+  // tokens, 432 -> 428 us, DeepSeek-shaped, 333 tokens, 254.4 -> 251.9). Above four entries a
+  // thread its rounds cost more than two launches (DeepSeek-shaped, 2000 tokens: 315 in three
+  // passes, 322 in one workgroup).
+  if (n <= kPermOneBlock) {
+    if (n <= kPermThreads)
+      hipLaunchKernelGGL(permute_one_kernel<1>, dim3(1), dim3(kPermThreads), 0, stream, idx, T, K, E, n_shared,
+                         tile_rows, pb);
+    else
+      hipLaunchKernelGGL(permute_one_kernel<kPermOneBlock / kPermThreads>, dim3(1), dim3(kPermThreads), 0, stream, idx,
+                         T, K, E, n_shared, tile_rows, pb);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(permute_count_kernel, dim3(n_chunks), dim3(kPermThreads), 0, stream, idx, n, E, chunk_counts);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
