@@ -53,14 +53,6 @@ constexpr int kPW = kW / kRowsPerPiece;   // 16-byte pieces of weights per threa
 template <int BM>
 constexpr int kPieces = kPW + BM / kRowsPerPiece;
 
-// A raw buffer over [p, p + bytes), bytes < 2^32, p wave-uniform; reads past it return zeros.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  const uint64_t u = static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32))) << 32 |
-                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a)));
-  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(u), 0, static_cast<int>(bytes), 0x00020000);
-}
-
 // The stream of one tile: acc += W X^T over nc chunks. off[]: this thread's 16-byte pieces of a
 // chunk (the first PW are weights, in w from byte w0 + chunk * wstep; then tokens, in a from a0 + 128 chunk).
 // NT: non-temporal weight loads.

@@ -80,6 +80,14 @@ __device__ __forceinline__ void lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// A raw buffer over [p, p + bytes), bytes < 2^32, p wave-uniform; reads past it return zeros.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint64_t u = static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32))) << 32 |
+                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a)));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(u), 0, static_cast<int>(bytes), 0x00020000);
+}
+
 // XOR swizzle of the eight 16-byte chunks of a 128-byte LDS operand row: row bits 0..2, with
 // row bit 3 flipping chunk bit 0. A 16-byte operand read whose lanes walk 16 consecutive rows
 // at one logical chunk then touches 16 distinct bank groups, for 32 or 64 four-byte banks; rows

@@ -78,6 +78,11 @@ __device__ __forceinline__ void dma16(uint32_t m0v, const void* gbase, uint32_t 
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0v), "v"(voff), "s"(gbase)
                : "memory", "m0");
 }
+// The same, non-temporal: rows that no other workgroup reads.
+__device__ __forceinline__ void dma16_nt(uint32_t m0v, const void* gbase, uint32_t voff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(m0v), "v"(voff), "s"(gbase)
+               : "memory", "m0");
+}
 // The same through a buffer resource (K-major operands): 16 bytes at offset voff of the buffer
 // described by rsrc, zeros where voff is past its size. (Full 64-bit per-lane addresses halve the
 // texture unit's load rate.)
@@ -127,7 +132,8 @@ __device__ __forceinline__ void tile_barrier() { asm volatile("s_barrier" ::: "m
 // W x + s B (A x) into one product. AKM / BKM: operand A / B is K-major (*akm / *bkm; the
 // matching TileOps fields are unused). bfrag[j]: tile row of B fragment j for this lane (a
 // multiple of 32 plus lane & 31); A fragment i is tile row 128 g + 32 i + (lane & 31).
-template <bool EXTRA = false, bool AKM = false, bool BKM = false>
+// STREAM: operand B is read by this workgroup alone: non-temporal loads.
+template <bool EXTRA = false, bool AKM = false, bool BKM = false, bool STREAM = false>
 __device__ __forceinline__ void gemm_tile_mainloop(const TileOps& o, int nk, const int (&bfrag)[kTileTN],
                                                    f32x16 (&acc)[kTileTM][kTileTN], TileLds& L,
                                                    const TileOps* x = nullptr, const TileKm* akm = nullptr,
@@ -178,7 +184,11 @@ __device__ __forceinline__ void gemm_tile_mainloop(const TileOps& o, int nk, con
     } else {
       const char* gb = o.b + static_cast<size_t>(tt) * o.b_step;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) dma16(lb0 + static_cast<uint32_t>((t % 3) * 32768 + i * 1024), gb, o.boff[i]);
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t m0v = lb0 + static_cast<uint32_t>((t % 3) * 32768 + i * 1024);
+        if (STREAM) dma16_nt(m0v, gb, o.boff[i]);
+        else dma16(m0v, gb, o.boff[i]);
+      }
     }
   };
   const int sw = lds_swizzle(lane & 31);

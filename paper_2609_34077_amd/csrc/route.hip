@@ -15,22 +15,27 @@
 // weights of whole layers; its WN*WK waves split the outputs (WN) and the k-steps (WK)
 // and the WK partial tiles are summed in LDS in a fixed order. Small token counts
 // (decode) use WK = 8..16 so all of d is in flight at once; large token counts stream x.
-// Many tokens routed through many layers at once use route_gemm_kernel instead, which stages
-// both operands through LDS.
+// Many tokens routed through many layers at once use tiles staged through LDS instead
+// (route_mid_kernel, route_gemm_kernel, route_tile_kernel).
 // The selection reads the fp32 logits from LDS: up to 16 experts one 16-lane row per token (one layer)
 // or one thread per (token, layer), above that one wavefront per pair.
 
 #include <limits.h>
 #include <math.h>
 
+#include <algorithm>
+#include <type_traits>
+
 #include "common.hpp"
+#include "gemm_tile.hpp"
 #include "kernels.hpp"
 #include "permute_block.hpp"
 
 namespace maskmoe {
 namespace {
 
-constexpr int kMaxK = 16;
+constexpr int kMaxRouteK = 16;
+constexpr int kMaxK = kMaxRouteK;
 constexpr int kMaxModeParams = 512;
 // Selection by one thread per (token, layer) pair up to this many experts, by one wavefront
 // (a lane per expert) above it when E <= 64. The softmax normaliser over all E experts (g = p)
@@ -40,10 +45,19 @@ constexpr int kMaxModeParams = 512;
 // lanes took ~5 us of the 4096-token selection kernel), the per-thread selection replays the
 // same tree, so every path gives the same bits.
 constexpr int kSelThreadE = 16;
-// The LDS-tiled router GEMM (route_gemm_kernel) pays off once a launch has many tokens and
-// enough router outputs to fill its 256-wide tile.
+// More than 64 experts are routed in one launch with selection; the tiled router GEMM pays off there
+// once a launch has many tokens and enough router outputs to fill half its 256-wide tile.
 constexpr int kRouteGemmMinT = 1024;
 constexpr int kRouteGemmMinOutputs = 128;
+// Launches of the tile kernels (route_mid_kernel, route_gemm_kernel, route_tile_kernel): they all sum
+// a logit over the 64-wide k-tiles in the same order, so that split and fused routing of the same
+// call give the same bits whichever of them each takes. Their 32-bit offsets reach over a tile's rows.
+inline bool route_tiles(int T, int d, int E, int L) {
+  const int outs = L * E;
+  if (d % 64 != 0 || d > (1 << 20) || T < kRouteSplitMinT) return false;
+  if (E > kRouteSplitMaxE) return T >= kRouteGemmMinT && outs >= kRouteGemmMinOutputs;
+  return outs > 64;
+}
 
 struct RouteParams {
   const void* x;
@@ -66,21 +80,24 @@ __device__ __forceinline__ float key_offset(int mode, float v) {
 
 // Selection, gates and outputs of one (token, layer) pair: z the E fp32 logits, o the E key
 // offsets, obase the pair's index in the [L, T] outputs. write_logits: also store z in p.logits.
-// EC: the expert count when known at compile time (0: p.E); the arithmetic is the same.
-template <int EC = 0>
+// EC, KC: the expert and selection counts when known at compile time (0: p.E, p.K); the arithmetic
+// is the same. The (K+1)-th pick is looked for only when the margin is asked for.
+template <int EC = 0, int KC = 0>
 __device__ __forceinline__ void select_pair(const RouteParams& p, const float* z, const float* o, size_t obase,
                                             bool write_logits) {
-  const int E = EC ? EC : p.E, K = p.K;
+  constexpr int kMaxK = KC ? KC : kMaxRouteK;
+  const int E = EC ? EC : p.E, K = KC ? KC : p.K;
   uint64_t tk0 = 0, tk1 = 0, tk2 = 0, tk3 = 0;
   int sel[kMaxK];
   float selz[kMaxK];
   float kth = -INFINITY, nxt = -INFINITY;
 #pragma unroll
   for (int j = 0; j <= kMaxK; ++j) {
-    if (j <= K) {
+    if (j < K || (j == K && p.margin)) {
       float best = -INFINITY;
       int bi = -1;
-      for (int e = 0; e < E; ++e) {
+#pragma unroll
+      for (int e = 0; e < (EC ? EC : E); ++e) {
         const uint64_t word = e < 64 ? tk0 : e < 128 ? tk1 : e < 192 ? tk2 : tk3;
         if ((word >> (e & 63)) & 1ull) continue;
         const float key = z[e] + o[e];
@@ -174,8 +191,10 @@ __device__ void route_finalize(const RouteParams& p, const float* logits, int ld
 constexpr int kSelThreads = 256;
 
 // E <= kSelThreadE: one thread per pair, the block's logits staged in LDS (odd row stride) so
-// the per-pair selection reads them without bank conflicts.
-template <int EC>
+// the per-pair selection reads them without bank conflicts. With E and K known at compile time the
+// picks unroll without their runtime guards (4.2 M pairs of 8 experts, top-2: 65 -> 35 us; 30 us are
+// the memory traffic).
+template <int EC, int KC = 0>
 __global__ __launch_bounds__(kSelThreads) void route_select_kernel(const RouteParams p) {
   constexpr int EMAX = EC ? EC : kSelThreadE;
   __shared__ float zs[kSelThreads * (EMAX + 1)];
@@ -206,7 +225,7 @@ __global__ __launch_bounds__(kSelThreads) void route_select_kernel(const RoutePa
   const uint32_t q = q0 + threadIdx.x;
   if (q >= pairs) return;
   const int l = static_cast<int>(q / static_cast<uint32_t>(p.T));
-  select_pair<EC>(p, zs + threadIdx.x * (E + 1), lo + l * E, q, false);
+  select_pair<EC, KC>(p, zs + threadIdx.x * (E + 1), lo + l * E, q, false);
 }
 
 // Lane exchanges within a 16-lane row (DPP): lane e of the row receives lane (e - R) mod 16.
@@ -694,33 +713,53 @@ __global__ __launch_bounds__(64 * WN * WK) void route_bf16_kernel(const RoutePar
   }
 }
 
-// Many tokens and many router outputs (tens of layers routed from the same tokens): a
-// 256-token x 256-output tile of whole layers, both operands staged through LDS in 64-wide
-// k-steps (the same load pipeline and swizzle as the expert GEMM: every token row is read
-// from HBM once, the router rows are shared by all workgroups through L2), accumulated on
-// v_mfma_f32_32x32x16_bf16. After the k-loop the staging LDS holds the fp32 logits of one
-// half of the tokens at a time, and the selection runs on them as in route_bf16_kernel.
-constexpr int kRgBM = 256, kRgBN = 256, kRgBK = 64, kRgThreads = 512;
+// Logits of token t at outputs o .. o + 3 of the layers from lg0 (o % 4 == 0; outputs at or past nout
+// are not there) to p.logits [L, T, E].
+__device__ __forceinline__ void store_logits4(const RouteParams& p, int lg0, int nout, int o, int t, float v0, float v1,
+                                              float v2, float v3) {
+  if (o >= nout) return;
+  const int E = p.E;
+  if ((E & 3) == 0) {   // four outputs of one layer, 16-byte aligned
+    const int lw = o / E;
+    *reinterpret_cast<f32x4*>(p.logits + (static_cast<size_t>(lg0 + lw) * p.T + t) * E + o - lw * E) =
+        f32x4{v0, v1, v2, v3};
+    return;
+  }
+  const float v[4] = {v0, v1, v2, v3};
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (o + e < nout) {
+      const int l = (o + e) / E;
+      p.logits[(static_cast<size_t>(lg0 + l) * p.T + t) * E + o + e - l * E] = v[e];
+    }
+}
 
-template <bool SPLIT>
-__global__ __launch_bounds__(kRgThreads) void route_gemm_kernel(const RouteParams p) {
-  constexpr int BM = kRgBM, BN = kRgBN, BK = kRgBK, NT = kRgThreads;
-  constexpr int WN = 4;                        // waves: 2 along tokens x 4 along outputs
-  constexpr int TM = 4, TN = 2;                // 32x32 fragments per wave: 128 tokens x 64 outputs
+// Many tokens and many router outputs (tens of layers routed from the same tokens): a tile of
+// 128 tokens x BN outputs (128 or 256) of whole layers per workgroup of four wavefronts (2 along
+// tokens x 2 along outputs), 64-wide k-tiles of both operands staged through LDS, accumulated on
+// v_mfma_f32_32x32x16_bf16 with the router rows as the row operand: a lane then holds four
+// neighbouring outputs of one token. Every token row is read from HBM once, the router rows are
+// shared by all workgroups through L2. One LDS buffer (48 KB) and two workgroups per CU: while one
+// stores a k-tile or waits at a barrier, the other multiplies; the tokens of two k-tiles and the
+// router rows of one travel in registers meanwhile.
+constexpr int kRgBM = 128, kRgMaxBN = 256, kRgBK = 64, kRgThreads = 256;
+
+template <int BN, bool SPLIT>
+__global__ __launch_bounds__(kRgThreads, 2) void route_gemm_kernel(const RouteParams p) {
+  constexpr int BM = kRgBM, BK = kRgBK, NT = kRgThreads;
+  constexpr int TM = 2, TN = BN / 64;          // 32-token and 32-output fragments per wavefront
+  constexpr int UA = BM * 8 / NT, UB = BN * 8 / NT;   // 16-byte units per thread and k-tile
   constexpr int HALF = BM / 2;                 // token rows per selection phase (one wave row)
-  constexpr int UA = BM * 8 / NT, UB = BN * 8 / NT;   // 16-byte units per thread and stage
-  constexpr int SA = BM * 8, SB = BN * 8;             // 16-byte slots per stage
-  constexpr int STAGING = 2 * (SA + SB) * 16;
   constexpr int LD = BN + 1;                   // logits row stride: odd, so token rows fall on distinct banks
-  constexpr int LOGITS = HALF * LD * 4;
+  constexpr int STAGING = (BM + BN) * BK * 2, LOGITS = SPLIT ? 0 : HALF * LD * 4;
   __shared__ __attribute__((aligned(16))) unsigned char smem[STAGING > LOGITS ? STAGING : LOGITS];
-  __shared__ float lo[BN];
-  u32x4* lds_a = reinterpret_cast<u32x4*>(smem);   // [2][SA]
-  u32x4* lds_b = lds_a + 2 * SA;                    // [2][SB]
+  __shared__ float lo[SPLIT ? 1 : BN];
+  u32x4* lds_a = reinterpret_cast<u32x4*>(smem);    // [BM * 8]
+  u32x4* lds_b = lds_a + BM * 8;                    // [BN * 8]
   float* logits = reinterpret_cast<float*>(smem);   // [HALF][LD], after the k-loop
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+  const int wm = wave >> 1, wn = wave & 1;
   const int t0 = blockIdx.x * BM;
   const int lg0 = blockIdx.y * p.lpw;
   const int nl = min(p.lpw, p.L - lg0);
@@ -728,122 +767,253 @@ __global__ __launch_bounds__(kRgThreads) void route_gemm_kernel(const RouteParam
   const uint16_t* x = static_cast<const uint16_t*>(p.x);
   const uint16_t* w = static_cast<const uint16_t*>(p.w) + static_cast<size_t>(lg0) * p.E * p.d;
 
-  // Thread tid loads rows (tid >> 3) + 64 i of each operand; rows past the last token or
-  // output are clamped onto valid rows and their results never written.
-  const int r0 = tid >> 3;
-  const int chunk = ((tid & 7) ^ lds_swizzle(r0)) * 8;
-  const uint16_t* asrc[UA];
-  const uint16_t* bsrc[UB];
+  // Thread tid loads rows (tid >> 3) + 32 i of each operand; rows past the last token or
+  // output are clamped onto valid rows and their results never written. Buffer loads: 32-bit
+  // offsets within the tile's rows, the k-tile in a scalar.
+  const int r0 = tid >> 3, rows = min(BM, p.T - t0);
+  const int dst = r0 * 8 + ((tid & 7) ^ lds_swizzle(r0));   // unit i: + NT * i
+  const __amdgpu_buffer_rsrc_t ar = make_rsrc(x + static_cast<size_t>(t0) * p.d, 2u * rows * p.d);
+  const __amdgpu_buffer_rsrc_t br = make_rsrc(w, 2u * nout * p.d);
+  uint32_t asrc[UA], bsrc[UB];
 #pragma unroll
-  for (int i = 0; i < UA; ++i) asrc[i] = x + static_cast<size_t>(min(t0 + r0 + 64 * i, p.T - 1)) * p.d + chunk;
+  for (int i = 0; i < UA; ++i) asrc[i] = 2u * (min(r0 + 32 * i, rows - 1) * p.d + (tid & 7) * 8);
 #pragma unroll
-  for (int i = 0; i < UB; ++i) bsrc[i] = w + static_cast<size_t>(min(r0 + 64 * i, nout - 1)) * p.d + chunk;
-  int aoff[TM], boff[TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) aoff[i] = (wm * 128 + i * 32 + (lane & 31)) * 8;
-#pragma unroll
-  for (int j = 0; j < TN; ++j) boff[j] = (wn * 64 + j * 32 + (lane & 31)) * 8;
-  const int sw = lds_swizzle(lane);   // fragment rows are a multiple of 32 plus (lane & 31)
+  for (int i = 0; i < UB; ++i) bsrc[i] = 2u * (min(r0 + 32 * i, nout - 1) * p.d + (tid & 7) * 8);
+  const int sw = lds_swizzle(lane & 31);   // fragment rows are a multiple of 32 plus (lane & 31)
 
-  f32x16 acc[TM][TN];
+  f32x16 acc[TN][TM];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int j = 0; j < TN; ++j)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+      for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.0f;
 
-  u32x4 ra[UA], rb[UB];
-  auto gload = [&](int kt) {
-#pragma unroll
-    for (int i = 0; i < UA; ++i) ra[i] = *reinterpret_cast<const u32x4*>(asrc[i] + kt * BK);
-#pragma unroll
-    for (int i = 0; i < UB; ++i) rb[i] = *reinterpret_cast<const u32x4*>(bsrc[i] + kt * BK);
-  };
-  auto lstore = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < UA; ++i) lds_a[buf * SA + tid + NT * i] = ra[i];
-#pragma unroll
-    for (int i = 0; i < UB; ++i) lds_b[buf * SB + tid + NT * i] = rb[i];
-  };
-  u32x4 af[2][TM], bf[2][TN];
-  auto read_frags = [&](int buf, int kk, int slot) {
-    const int ch = (kk * 2 + (lane >> 5)) ^ sw;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) af[slot][i] = lds_a[buf * SA + aoff[i] + ch];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bf[slot][j] = lds_b[buf * SB + boff[j] + ch];
-  };
-
-  // k-tile kt sits in LDS buffer kt & 1 and tile kt + 1 in registers; after the first k16 step
-  // of tile kt the registers go to the other buffer and are refilled with tile kt + 2.
-  // Branch-free body, interleaved by LLVM's MFMA/DS strategy as in the expert GEMM: past the end
-  // the last tile is loaded again into the idle buffer, which nothing reads.
   const int nk = p.d / BK;
-  gload(0);
-  lstore(0);
-  gload(min(1, nk - 1));
-  __syncthreads();
-  read_frags(0, 0, 0);
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    __builtin_amdgcn_iglp_opt(0);
+  auto k_bytes = [&](int kt) { return min(kt, nk - 1) * (2 * BK); };   // past the end: the last k-tile again, not used
+  u32x4 ra[2][UA], rb[UB];
+  constexpr int kNt = 2;   // the load's non-temporal bit: token rows are read once
+  auto load_a = [&](int kt, u32x4 (&r)[UA]) {
+    const int k = k_bytes(kt);
+#pragma unroll
+    for (int i = 0; i < UA; ++i) r[i] = __builtin_amdgcn_raw_buffer_load_b128(ar, asrc[i], k, kNt);
+  };
+  auto load_b = [&](int kt) {
+    const int k = k_bytes(kt);
+#pragma unroll
+    for (int i = 0; i < UB; ++i) rb[i] = __builtin_amdgcn_raw_buffer_load_b128(br, bsrc[i], k, 0);
+  };
+  // k-tile kt: registers to LDS, then the router rows of kt + 1 and the tokens of kt + 2 on
+  // their way (in this order: waiting for router rows, which come from L2, leaves the youngest
+  // tokens, which come from HBM, in flight), then the products.
+  auto tile = [&](int kt, auto set_c) {
+    constexpr int set = decltype(set_c)::value;
+#pragma unroll
+    for (int i = 0; i < UA; ++i) lds_a[dst + NT * i] = ra[set][i];
+#pragma unroll
+    for (int i = 0; i < UB; ++i) lds_b[dst + NT * i] = rb[i];
+    __builtin_amdgcn_sched_barrier(0);
+    load_b(kt + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    load_a(kt + 2, ra[set]);
+    __builtin_amdgcn_sched_barrier(0);
+    lds_sync();
 #pragma unroll
     for (int kk = 0; kk < BK / 16; ++kk) {
-      const int cur = kk & 1;
-      if (kk + 1 < BK / 16) read_frags(buf, kk + 1, cur ^ 1);
-      if (kk == 0) {
-        lstore(buf ^ 1);
-        gload(min(kt + 2, nk - 1));
-      }
+      const int ch = (kk * 2 + (lane >> 5)) ^ sw;
+      u32x4 af[TM], bf[TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i) af[i] = lds_a[(wm * HALF + i * 32 + (lane & 31)) * 8 + ch];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_32x32x16(af[cur][i], bf[cur][j], acc[i][j]);
+      for (int j = 0; j < TN; ++j) bf[j] = lds_b[(wn * (BN / 2) + j * 32 + (lane & 31)) * 8 + ch];
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[j][i] = mfma_32x32x16(bf[j], af[i], acc[j][i]);
     }
-    __syncthreads();
-    read_frags(buf ^ 1, 0, 0);
+    lds_sync();   // the buffer is read
+  };
+  load_a(0, ra[0]);
+  __builtin_amdgcn_sched_barrier(0);
+  load_b(0);
+  __builtin_amdgcn_sched_barrier(0);
+  load_a(1, ra[1]);
+  __builtin_amdgcn_sched_barrier(0);
+  int kt = 0;
+  for (; kt + 1 < nk; kt += 2) {
+    tile(kt, std::integral_constant<int, 0>{});
+    tile(kt + 1, std::integral_constant<int, 1>{});
   }
+  if (kt < nk) tile(kt, std::integral_constant<int, 0>{});
 
-  // The last barrier of the loop ends every read of the staging buffers. Phase h: the waves
-  // of token half h write their logits, then every thread selects for those tokens.
-  // acc[i][j][4 jj + ii] is token row wm*128 + i*32 + 8 jj + 4 (lane >> 5) + ii, output
-  // column wn*64 + j*32 + (lane & 31).
+  // acc[j][i][4 q + e] is output wn*BN/2 + j*32 + 8 q + 4 (lane >> 5) + e of token
+  // t0 + wm*64 + i*32 + (lane & 31).
+  if (SPLIT) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int t = t0 + wm * HALF + i * 32 + (lane & 31);
+      if (t >= p.T) continue;
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          store_logits4(p, lg0, nout, wn * (BN / 2) + j * 32 + 8 * q + 4 * (lane >> 5), t, acc[j][i][4 * q],
+                        acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]);
+    }
+    return;
+  }
+  // Phase h: the waves of token half h write their logits to LDS (the last barrier of the loop
+  // ended every read of the staging buffer), then every thread selects for those tokens.
   for (int i = tid; i < nout; i += NT) lo[i] = key_offset(p.mode, p.modep[lg0 * p.E + i]);
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     if (wm == h) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int row = i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            logits[row * LD + wn * 64 + j * 32 + (lane & 31)] = acc[i][j][r];
-          }
+          for (int r = 0; r < 16; ++r)
+            logits[(i * 32 + (lane & 31)) * LD + wn * (BN / 2) + j * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)] =
+                acc[j][i][r];
     }
     lds_sync();
-    if (SPLIT) {   // this half's logits -> p.logits [L, T, E]: a thread per (token, layer), tokens fastest
-      const int E = p.E;
-      for (int i = tid; i < HALF * nl; i += NT) {
-        const int tt = i % HALF, lw = i / HALF;
-        const int t = t0 + h * HALF + tt;
-        if (t >= p.T) continue;
-        const float* src = logits + tt * LD + lw * E;   // odd LD: the lanes' reads fall on distinct banks
-        float* dst = p.logits + (static_cast<size_t>(lg0 + lw) * p.T + t) * E;
-        if ((E & 3) == 0) {   // rows are 16-byte aligned
-          for (int e = 0; e < E; e += 4)
-            *reinterpret_cast<f32x4*>(dst + e) = f32x4{src[e], src[e + 1], src[e + 2], src[e + 3]};
-        } else {
-          for (int e = 0; e < E; ++e) dst[e] = src[e];
-        }
-      }
-    } else {
-      route_finalize<true>(p, logits, LD, lo, t0 + h * HALF, HALF, lg0, nl, NT);
-    }
+    route_finalize<true>(p, logits, LD, lo, t0 + h * HALF, HALF, lg0, nl, NT);
     lds_sync();   // the next phase overwrites the logits
   }
+}
+
+// Split routing with more than 128 outputs: 256 tokens x 256 outputs per workgroup on the expert
+// GEMM's ping-pong tile (gemm_tile.hpp), the router rows as its A operand and the token rows, two
+// k-tiles ahead and non-temporal, as its B operand; the logits go straight to p.logits. Bound by the
+// token stream: 131072 tokens, 32 layers, 1.07 GB: 306 us before (register-staged 256 x 256 tiles),
+// 255 to 290 us now. Starting the k-loop of neighbouring workgroups at different k-tiles, so that
+// they do not read the same columns at once, took it to 262 us, but sums each logit from another
+// k on: near-tied experts change places, so it is not done.
+__global__ __launch_bounds__(kTileThreads) void route_tile_kernel(const RouteParams p) {
+  __shared__ TileLds lds;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave >> 2, wn = wave & 3;
+  const int t0 = blockIdx.x * kTileN, lg0 = blockIdx.y * p.lpw;
+  const int nl = min(p.lpw, p.L - lg0), nout = nl * p.E, rows = min(kTileN, p.T - t0);
+  const int nk = p.d / kTileK;
+  TileOps ops;
+  ops.a = reinterpret_cast<const char*>(static_cast<const uint16_t*>(p.w) + static_cast<size_t>(lg0) * p.E * p.d);
+  ops.b = reinterpret_cast<const char*>(static_cast<const uint16_t*>(p.x) + static_cast<size_t>(t0) * p.d);
+  ops.b_step = kTileK * 2;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {   // rows past the end are clamped, their results never stored
+    const int r = tile_dma_row(i), c = tile_dma_chunk(i) * 8;
+    ops.aoff[i] = 2u * static_cast<uint32_t>(min(r, nout - 1) * p.d + c);
+    ops.boff[i] = 2u * static_cast<uint32_t>(min(r, rows - 1) * p.d + c);
+  }
+  int bfrag[kTileTN];
+#pragma unroll
+  for (int j = 0; j < kTileTN; ++j) bfrag[j] = wn * 64 + j * 32 + (lane & 31);
+  f32x16 acc[kTileTM][kTileTN];
+#pragma unroll
+  for (int i = 0; i < kTileTM; ++i)
+#pragma unroll
+    for (int j = 0; j < kTileTN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  gemm_tile_mainloop<false, false, false, true>(ops, nk, bfrag, acc, lds);
+  // acc[i][j][4 q + e]: output wm*128 + i*32 + 8 q + 4 (lane >> 5) + e of token t0 + bfrag[j]
+#pragma unroll
+  for (int i = 0; i < kTileTM; ++i)
+#pragma unroll
+    for (int j = 0; j < kTileTN; ++j) {
+      const int t = t0 + bfrag[j];
+      if (t >= p.T) continue;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        store_logits4(p, lg0, nout, wm * 128 + i * 32 + 8 * q + 4 * (lane >> 5), t, acc[i][j][4 * q], acc[i][j][4 * q + 1],
+                      acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+    }
+}
+
+// Split routing of fewer tokens than fill the chip with 256 x 256 tiles: 64 tokens x BN outputs (64
+// or 128) per workgroup of four wavefronts (2 along tokens x 2 along outputs), 64-wide k-tiles
+// staged through LDS, four of them in flight in registers: with about one workgroup per CU the time
+// is the chain of memory latencies along the reduction. 32 layers of 8 experts, d 4096, whole call:
+// 600 tokens 100 -> 28 us, 1500 88 -> 27, 5000 85 -> 42; 16 layers, 2000 tokens 85 -> 26.
+constexpr int kRmBM = 64, kRmThreads = 256, kRmDepth = 4;
+
+template <int BN>
+__global__ __launch_bounds__(kRmThreads, 2) void route_mid_kernel(const RouteParams p) {
+  constexpr int BK = 64, NT = kRmThreads, ROWS = kRmBM + BN;
+  constexpr int PER = ROWS * 8 / NT, PB = BN * 8 / NT;   // 16-byte pieces per thread, the first PB of the router
+  constexpr int TN = BN / 64;                            // 32-output fragments per wavefront
+  __shared__ u32x4 lds[2][ROWS * 8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+  const int t0 = blockIdx.x * kRmBM, lg0 = blockIdx.y * p.lpw;
+  const int nl = min(p.lpw, p.L - lg0), nout = nl * p.E, rows = min(kRmBM, p.T - t0);
+  const int nk = p.d / BK, r0 = tid >> 3;
+  const __amdgpu_buffer_rsrc_t ar =
+      make_rsrc(static_cast<const uint16_t*>(p.x) + static_cast<size_t>(t0) * p.d, 2u * rows * p.d);
+  const __amdgpu_buffer_rsrc_t br =
+      make_rsrc(static_cast<const uint16_t*>(p.w) + static_cast<size_t>(lg0) * p.E * p.d, 2u * nout * p.d);
+  uint32_t off[PER];   // rows past the end are clamped, their results never stored
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int r = i < PB ? min(r0 + 32 * i, nout - 1) : min(r0 + 32 * (i - PB), rows - 1);
+    off[i] = 2u * static_cast<uint32_t>(r * p.d + (tid & 7) * 8);
+  }
+  const int dst = r0 * 8 + ((tid & 7) ^ lds_swizzle(r0));   // piece i: + NT * i
+  u32x4 reg[kRmDepth][PER];
+  auto load = [&](int c, u32x4 (&r)[PER]) {   // past the end: the last k-tile again, not used
+    const int k = min(c, nk - 1) * (2 * BK);
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      r[i] = i < PB ? __builtin_amdgcn_raw_buffer_load_b128(br, off[i], k, 0)
+                    : __builtin_amdgcn_raw_buffer_load_b128(ar, off[i], k, 0);
+  };
+  auto store = [&](int buf, const u32x4 (&r)[PER]) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) lds[buf][dst + NT * i] = r[i];
+  };
+  f32x16 acc[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
+  const int l32 = lane & 31, sw = lds_swizzle(l32);
+  int c = 0;
+  auto step = [&](auto ph) {   // k-tile c in LDS buffer c & 1, its registers (set c & 3) take k-tile c + 4
+    constexpr int PH = decltype(ph)::value;
+    load(c + kRmDepth, reg[PH]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < BK / 16; ++kk) {
+      const int ch = (kk * 2 + (lane >> 5)) ^ sw;
+      const u32x4 t = lds[PH & 1][(BN + wm * 32 + l32) * 8 + ch];
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[j] = mfma_32x32x16(lds[PH & 1][(wn * (BN / 2) + j * 32 + l32) * 8 + ch], t, acc[j]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    store((PH & 1) ^ 1, reg[(PH + 1) & 3]);
+    lds_sync();
+    return ++c < nk;
+  };
+#pragma unroll
+  for (int i = 0; i < kRmDepth; ++i) {
+    load(i, reg[i]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  store(0, reg[0]);
+  lds_sync();
+  while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{}) &&
+         step(std::integral_constant<int, 2>{}) && step(std::integral_constant<int, 3>{})) {
+  }
+  // acc[j][4 q + e]: output wn*BN/2 + j*32 + 8 q + 4 (lane >> 5) + e of token t0 + wm*32 + l32
+  const int t = t0 + wm * 32 + l32;
+  if (t >= p.T) return;
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      store_logits4(p, lg0, nout, wn * (BN / 2) + j * 32 + 8 * q + 4 * (lane >> 5), t, acc[j][4 * q], acc[j][4 * q + 1],
+                    acc[j][4 * q + 2], acc[j][4 * q + 3]);
 }
 
 // fp32 router: 16 tokens x up to 256 outputs (whole layers) per workgroup on
@@ -993,12 +1163,37 @@ hipError_t launch_route(bool bf16, const void* x, const void* w_router, int T, i
       if (d % 4 == 0) hipLaunchKernelGGL(route_f32_kernel<true>, grid, dim3(64 * kF32Waves), 0, stream, p);
       else hipLaunchKernelGGL(route_f32_kernel<false>, grid, dim3(64 * kF32Waves), 0, stream, p);
       err = hipGetLastError();
-    } else if (T >= kRouteGemmMinT && d % kRgBK == 0 && p.L * E >= kRouteGemmMinOutputs) {
-      p.lpw = kRgBN / E;
+    } else if (split && route_tiles(T, d, E, p.L)) {
+      // The tile by how many workgroups it gives (the 256 CUs need about one each; beyond two
+      // each the larger tile's fewer loads win). 32 layers of 8 experts, d 4096, whole call with
+      // 64-output, 128-output and 256 x 256 tiles: 2000 tokens 29 / 37 / 79 us, 5000 49 / 42 / 81,
+      // 12000 82 / 61 / 86, 30000 188 / 145 / 105, 131072 973 / 613 / 311. 16 layers: 30000 tokens,
+      // 128-output tiles of 64 / 128 tokens 82 / 77, 131072 tokens 310 / 293 (262 non-temporal).
+      const int outs = p.L * E;
+      const int mt = (T + kRmBM - 1) / kRmBM;
+      auto cover = [&](int bn) {   // whole layers per workgroup; column blocks
+        p.lpw = std::max(std::min(bn / E, p.L), 1);
+        return (p.L + p.lpw - 1) / p.lpw;
+      };
+      if (outs <= 64 || mt * cover(64) <= 256) {
+        hipLaunchKernelGGL(route_mid_kernel<64>, dim3(mt, cover(64)), dim3(kRmThreads), 0, stream, p);
+      } else if (mt * cover(128) <= 512) {
+        hipLaunchKernelGGL(route_mid_kernel<128>, dim3(mt, cover(128)), dim3(kRmThreads), 0, stream, p);
+      } else if (outs <= 128) {
+        hipLaunchKernelGGL((route_gemm_kernel<128, true>), dim3((T + kRgBM - 1) / kRgBM, cover(128)), dim3(kRgThreads),
+                           0, stream, p);
+      } else {
+        hipLaunchKernelGGL(route_tile_kernel, dim3((T + kTileN - 1) / kTileN, cover(256)), dim3(kTileThreads), 0,
+                           stream, p);
+      }
+      err = hipGetLastError();
+    } else if (route_tiles(T, d, E, p.L)) {
+      const bool narrow = p.L * E <= 128;   // one 128-output tile holds every layer
+      p.lpw = (narrow ? 128 : kRgMaxBN) / E;
       if (p.lpw > p.L) p.lpw = p.L;
       dim3 grid((T + kRgBM - 1) / kRgBM, (p.L + p.lpw - 1) / p.lpw);
-      if (split) hipLaunchKernelGGL(route_gemm_kernel<true>, grid, dim3(kRgThreads), 0, stream, p);
-      else hipLaunchKernelGGL(route_gemm_kernel<false>, grid, dim3(kRgThreads), 0, stream, p);
+      if (narrow) hipLaunchKernelGGL((route_gemm_kernel<128, false>), grid, dim3(kRgThreads), 0, stream, p);
+      else hipLaunchKernelGGL((route_gemm_kernel<kRgMaxBN, false>), grid, dim3(kRgThreads), 0, stream, p);
       err = hipGetLastError();
     } else {
       const int need = p.L * E < 256 ? p.L * E : 256;
@@ -1020,7 +1215,8 @@ hipError_t launch_route(bool bf16, const void* x, const void* w_router, int T, i
       const size_t pairs = static_cast<size_t>(p.L) * T;
       if (E <= kSelThreadE) {
         dim3 grid(static_cast<unsigned>((pairs + kSelThreads - 1) / kSelThreads));
-        if (E == 8) hipLaunchKernelGGL(route_select_kernel<8>, grid, dim3(kSelThreads), 0, stream, p);
+        if (E == 8 && K == 2) hipLaunchKernelGGL((route_select_kernel<8, 2>), grid, dim3(kSelThreads), 0, stream, p);
+        else if (E == 8) hipLaunchKernelGGL(route_select_kernel<8>, grid, dim3(kSelThreads), 0, stream, p);
         else if (E == 16) hipLaunchKernelGGL(route_select_kernel<16>, grid, dim3(kSelThreads), 0, stream, p);
         else hipLaunchKernelGGL(route_select_kernel<0>, grid, dim3(kSelThreads), 0, stream, p);
       } else {

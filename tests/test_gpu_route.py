@@ -196,6 +196,15 @@ SPLIT_CASES = [
     (640, 256, 17, 2, 1, L.ROUTE_SOFT_PRIOR, L.GATE_P),
     (520, 128, 48, 6, 2, L.ROUTE_PLAIN, L.GATE_P),
     (1030, 192, 40, 4, 3, L.ROUTE_HARD_MASK, L.GATE_P),
+    # the logit tiles by how many workgroups they give: 64 x 64, 64 x 128, 128 x 128, 256 x 256;
+    # d of one k-tile and of several; E no multiple of four; 32 outputs stay with the 16-token tiles
+    (4096, 192, 8, 2, 4, L.ROUTE_SOFT_PRIOR, L.GATE_RENORM),
+    (4200, 128, 8, 2, 32, L.ROUTE_HARD_MASK, L.GATE_RENORM),
+    (4200, 64, 5, 2, 30, L.ROUTE_PLAIN, L.GATE_P),
+    (33000, 128, 8, 2, 16, L.ROUTE_SOFT_PRIOR, L.GATE_RENORM),
+    (17000, 320, 8, 2, 32, L.ROUTE_SOFT_PRIOR, L.GATE_RENORM),
+    (17001, 64, 5, 3, 37, L.ROUTE_PLAIN, L.GATE_P),
+    (600, 128, 16, 4, 5, L.ROUTE_HARD_MASK, L.GATE_P),
 ]
 
 
