@@ -27,8 +27,15 @@
 // reductions per miss. The selected sets of kSegChunk steps of every stream are first built in
 // LDS (an LDS OR per valid entry); a set of fewer than K experts flags an invalid or repeated
 // entry.
+//
+// Up to 8 experts, top-2, LRU or FIFO (cache_list_kernel): one lane per stream. The cache is a list
+// of 4-bit expert ids, oldest first, in one register; a step finds, deletes and appends ids with a
+// few bit operations and no lane exchanges. One wavefront of the workgroup replays 64 streams while
+// the others turn the next chunk of the traces into sorted pairs in LDS.
 
 #include <limits.h>
+
+#include <type_traits>
 
 #include "cache_step.hpp"
 #include "common.hpp"
@@ -345,6 +352,214 @@ __global__ __launch_bounds__(64) void cache_seg_kernel(
   }
 }
 
+// ---- one lane per stream: E <= 8, K = 2, LRU or FIFO
+//
+// list: the cached experts' ids, oldest in the low nibble, 0xf past the nc4 / 4 cached ones. A step
+// takes its two experts in ascending order as words of eight equal nibbles (ra, rb); an entry that is
+// invalid or repeats the first comes as nibble 8, after the valid ones. The list after a step:
+//   LRU   the experts not selected, in order, less the evicted ones at the front; then the hits, then
+//         the misses, each in ascending order;
+//   FIFO  the list less the evicted ones (the oldest not selected), then the misses.
+// About 53 instructions a step, which one wavefront issues in ~300 cycles: 8192 streams of 512 steps
+// 121 us with eight lanes per stream, 66 us this way (LRU); the streams run side by side, so the time
+// is that of one stream's steps.
+constexpr int kListThreads = 512, kListSteps = 64, kListStreams = 64;
+constexpr int kListPitch = kListStreams + 1;   // 8-byte units per step: the producers' stores spread over the banks
+
+// Bits of the list in front of the first nibble of `list` equal to those of r: 28 when there is
+// none (found is then false).
+__device__ __forceinline__ int list_find(uint32_t list, uint32_t r, bool& found) {
+  const uint32_t x = list ^ r;
+  const uint32_t t = (x - 0x11111111u) & ~x & 0x88888888u;   // its lowest set bit marks the first zero nibble of x
+  found = t != 0;
+  return __builtin_ctz(t | 0x80000000u) - 3;
+}
+// The list without the nibble at bit p.
+__device__ __forceinline__ uint32_t list_delete(uint32_t list, int p) {
+  const uint32_t front = (1u << p) - 1u;
+  return (list & front) | (__builtin_amdgcn_alignbit(~0u, list, 4) & ~front);
+}
+
+// One step; ALL: both entries are valid in every lane. h4, m4: four times the hits and misses.
+template <int POLICY, bool ALL>
+__device__ __forceinline__ void list_step(uint32_t ra, uint32_t rb, int B4, uint32_t& list, int& nc4, int& h4, int& m4) {
+  const int nv4 = ALL ? 8 : ((ra & 8u) ? 0 : 4) + ((rb & 8u) ? 0 : 4);
+  bool ha, hb;
+  if (POLICY == 0) {
+    const int pa = list_find(list, ra, ha);
+    uint32_t l = ha ? list_delete(list, pa) : list;
+    const int pb = list_find(l, rb, hb);
+    l = hb ? list_delete(l, pb) : l;
+    h4 = (ha ? 4 : 0) + (hb ? 4 : 0);
+    m4 = nv4 - h4;
+    const int rest4 = nc4 - h4;
+    const int ev4 = max(rest4 + nv4 - B4, 0);      // at most 8: rest4 <= B4 - h4
+    l = __builtin_amdgcn_alignbit(~0u, l, ev4);
+    const int len4 = rest4 - ev4;                   // the selected experts follow, at most 32 - nv4
+    const bool swap = hb && !ha;                    // hits before misses
+    const uint32_t first = swap ? rb : ra, second = swap ? ra : rb;
+    const uint32_t pair = (first & 0x0fu) | (second & 0xf0u);
+    const uint32_t keep = ALL ? 0xffu : (1u << nv4) - 1u;   // invalid entries come last
+    list = l ^ (((pair ^ 0xffu) & keep) << (len4 & 31));
+    nc4 = len4 + nv4;
+  } else {
+    const int pa = list_find(list, ra, ha), pb = list_find(list, rb, hb);
+    h4 = (ha ? 4 : 0) + (hb ? 4 : 0);
+    m4 = nv4 - h4;
+    const int ev4 = max(nc4 + m4 - B4, 0);
+    // one hit: at most one eviction, of the oldest or, when that is the hit, of the one behind it
+    const bool behind = (ha && pa == 0) || (hb && pb == 0);
+    const uint32_t one = list_delete(list, behind ? 4 : 0);
+    uint32_t l = h4 == 4 && ev4 ? one : __builtin_amdgcn_alignbit(~0u, list, h4 ? 0 : ev4);
+    const int len4 = nc4 - (h4 == 8 ? 0 : ev4);
+    const uint32_t pair = ha ? rb & 0xffu : (ra & 0x0fu) | (rb & 0xf0u);   // the misses, in order
+    const uint32_t keep = (1u << m4) - 1u;
+    list = l ^ (((pair ^ 0xffu) & keep) << (len4 & 31));
+    nc4 = len4 + m4;
+  }
+}
+
+template <int POLICY>   // 0 LRU, 2 FIFO
+__global__ __launch_bounds__(kListThreads) void cache_list_kernel(
+    const int32_t* __restrict__ trace, long nstreams, int N, int E, int B, int32_t* __restrict__ state,
+    int64_t* __restrict__ fetches, int64_t* __restrict__ hits, uint8_t* __restrict__ f_per_step,
+    int32_t* __restrict__ dev_error, bool vec) {
+  __shared__ uint2 sel[2][kListSteps * kListPitch];             // (ra, rb) of [step][stream]
+  __shared__ uint32_t fbuf[2][kListSteps / 4 * kListPitch];     // misses of four steps, [step / 4][stream]
+  __shared__ int odd[2];                                        // the chunk has an invalid or repeated entry
+  constexpr int kProd = kListThreads - 64;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const long stream0 = static_cast<long>(blockIdx.x) * kListStreams;
+  const int ns = static_cast<int>(min(static_cast<long>(kListStreams), nstreams - stream0));
+  const int chunks = (N + kListSteps - 1) / kListSteps;
+  const bool consumer = tid < 64;
+  const bool live = lane < ns;
+
+  // steps n0 .. n0 + 63 of every stream as sorted pairs; lanes take neighbouring steps of a stream
+  auto produce = [&](int c) {
+    const int n0 = c * kListSteps, steps = min(kListSteps, N - n0);
+    constexpr int U = (kListSteps * kListStreams + kProd - 1) / kProd;
+    int2 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = tid - 64 + u * kProd, st = i / kListSteps, n = i % kListSteps;
+      v[u] = make_int2(0, 1);   // streams and steps that are not there: any valid pair
+      if (i < kListSteps * kListStreams && st < ns && n < steps) {
+        const int32_t* p = trace + ((stream0 + st) * N + n0 + n) * 2;
+        if (vec) v[u] = *reinterpret_cast<const int2*>(p);
+        else v[u] = make_int2(p[0], p[1]);
+      }
+    }
+    bool any = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = tid - 64 + u * kProd, st = i / kListSteps, n = i % kListSteps;
+      if (i >= kListSteps * kListStreams) continue;
+      const bool va = v[u].x >= 0 && v[u].x < E, vb = v[u].y >= 0 && v[u].y < E && !(va && v[u].y == v[u].x);
+      const uint32_t a = va ? v[u].x : 8, b = vb ? v[u].y : 8;   // 8 sorts behind every expert
+      any = any || !va || !vb;
+      sel[c & 1][n * kListPitch + st] = make_uint2(min(a, b) * 0x11111111u, max(a, b) * 0x11111111u);
+    }
+    if (any) odd[c & 1] = 1;
+  };
+
+  uint32_t list = ~0u;
+  int nc4 = 0;
+  const int B4 = 4 * min(B, 8);   // E <= 8: more slots never evict
+  bool bad = false;
+  if (tid < 2) odd[tid] = 0;
+  __syncthreads();
+  if (consumer) {
+    if (state && live)
+      for (int s = 0; s < B; ++s) {   // slots are listed oldest first
+        const int e = state[(stream0 + lane) * B + s];
+        bool dup = false;
+        if (e >= 0 && e < E) list_find(list, static_cast<uint32_t>(e) * 0x11111111u, dup);
+        if (e >= 0 && e < E && !dup) {
+          list ^= (static_cast<uint32_t>(e) ^ 0xfu) << nc4;
+          nc4 += 4;
+        } else if (e >= 0) {
+          bad = true;
+        }
+      }
+  } else {
+    produce(0);
+  }
+  __syncthreads();
+  long tot_f = 0, tot_h = 0;
+  for (int c = 0; c < chunks; ++c) {
+    const int buf = c & 1, n0 = c * kListSteps, steps = min(kListSteps, N - n0);
+    if (consumer) {
+      __builtin_amdgcn_s_setprio(3);
+      const bool all = odd[buf] == 0;
+      int f4 = 0, h4s = 0;
+      const uint2* row = &sel[buf][lane];
+      auto replay = [&](auto all_c) {
+        constexpr bool ALL = decltype(all_c)::value;
+        uint2 nx[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) nx[q] = row[q * kListPitch];
+        for (int g = 0; g < (steps + 3) / 4; ++g) {   // steps past the last one fall out of the counts below
+          uint2 cur[4];
+          const int gn = min(g + 1, kListSteps / 4 - 1);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            cur[q] = nx[q];
+            nx[q] = row[(4 * gn + q) * kListPitch];
+          }
+          uint32_t word = 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if (4 * g + q >= steps) break;
+            int h4, m4;
+            list_step<POLICY, ALL>(cur[q].x, cur[q].y, B4, list, nc4, h4, m4);
+            h4s += h4;
+            f4 += m4;
+            word |= static_cast<uint32_t>(m4 >> 2) << (8 * q);
+          }
+          if (f_per_step) fbuf[buf][g * kListPitch + lane] = word;
+        }
+      };
+      if (all) replay(std::true_type{});
+      else replay(std::false_type{});
+      tot_f += f4 / 4;
+      tot_h += h4s / 4;
+      bad = bad || !all;
+      __builtin_amdgcn_s_setprio(0);
+    } else {
+      if (c + 1 < chunks) produce(c + 1);
+      if (f_per_step && c > 0) {   // the misses of the chunk before, bytes of [stream][step]
+        for (int i = tid - 64; i < kListSteps * kListStreams; i += kProd) {
+          const int st = i / kListSteps, n = i % kListSteps;
+          if (st < ns)
+            f_per_step[(stream0 + st) * N + n0 - kListSteps + n] =
+                static_cast<uint8_t>(fbuf[buf ^ 1][n / 4 * kListPitch + st] >> (8 * (n & 3)));
+        }
+      }
+    }
+    __syncthreads();
+    if (tid == 64) odd[buf] = 0;   // read by the consumer before the barrier, set again after the next one
+    __syncthreads();
+  }
+  if (f_per_step) {
+    const int c = chunks - 1, n0 = c * kListSteps, steps = N - n0;
+    for (int i = tid; i < kListSteps * kListStreams; i += kListThreads) {
+      const int st = i / kListSteps, n = i % kListSteps;
+      if (st < ns && n < steps)
+        f_per_step[(stream0 + st) * N + n0 + n] =
+            static_cast<uint8_t>(fbuf[c & 1][n / 4 * kListPitch + st] >> (8 * (n & 3)));
+    }
+  }
+  if (!consumer) return;
+  if (bad && dev_error) *dev_error = 1;
+  if (!live) return;
+  fetches[stream0 + lane] = tot_f;
+  hits[stream0 + lane] = tot_h;
+  if (state)
+    for (int s = 0; s < B; ++s)
+      state[(stream0 + lane) * B + s] = 4 * s < nc4 ? static_cast<int>((list >> (4 * s)) & 0xfu) : -1;
+}
+
 template <int POLICY>
 void launch_cache_policy(const int32_t* trace, int L, int S, int N, int K, int E, int B, int32_t* state,
                          int32_t* counts, int64_t* fetches, int64_t* hits, uint8_t* f_per_step, int32_t* dev_error,
@@ -356,6 +571,12 @@ void launch_cache_policy(const int32_t* trace, int L, int S, int N, int K, int E
     const dim3 grid(static_cast<unsigned>((streams + kCacheWavesPerBlock - 1) / kCacheWavesPerBlock));
     hipLaunchKernelGGL(cache_kernel<POLICY>, grid, dim3(64 * kCacheWavesPerBlock), 0, stream, trace, L, S, N, K, E,
                        B, state, counts, fetches, hits, f_per_step, dev_error);
+  } else if (POLICY != 1 && E <= 8 && K == 2) {
+    const bool vec = (reinterpret_cast<uintptr_t>(trace) & 7) == 0;
+    const dim3 grid(static_cast<unsigned>((streams + kListStreams - 1) / kListStreams));
+    if constexpr (POLICY != 1)
+      hipLaunchKernelGGL((cache_list_kernel<POLICY>), grid, dim3(kListThreads), 0, stream, trace, streams, N, E, B, state,
+                         fetches, hits, f_per_step, dev_error, vec);
   } else if (E <= 8) {
     const dim3 grid(static_cast<unsigned>((streams + 7) / 8));
     hipLaunchKernelGGL((cache_seg_kernel<POLICY, 8>), grid, dim3(64), 0, stream, trace, L, S, N, K, E, B, state,

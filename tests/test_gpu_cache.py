@@ -301,3 +301,27 @@ def test_invalid_entries_long_trace(E):
     g = _compare(tr, E, 4)
     assert int(g["dev_error"][0]) == 1
     assert g["f_per_step"][0, 1, 5] <= 2 and g["f_per_step"][1, 0, 70] <= 1
+
+
+@pytest.mark.parametrize("policy", [L.CACHE_LRU, L.CACHE_FIFO])
+@pytest.mark.parametrize("E,B,N,S,locality", [(8, 4, 64, 64, 0.5), (8, 2, 65, 65, 0.3), (8, 8, 127, 63, 0.6), (8, 20, 128, 1, 0.2),
+                                              (8, 7, 200, 130, 0.1), (2, 2, 64, 3, 0.5), (3, 2, 191, 70, 0.0),
+                                              (5, 3, 66, 129, 0.7)])
+def test_list_replay_edges(policy, E, B, N, S, locality):
+    """Top-2 replays of up to 8 experts (one lane per stream): chunk and stream counts around 64, the
+    smallest and never-evicting caches, a given state, invalid and repeated entries in some
+    streams, and a trace that starts on an odd 4-byte word."""
+    tr = synth.random_trace(1, S, N, 2, E, seed=E * 100 + B * 10 + N + S, locality=locality)
+    _compare(tr, E, B, policy=policy)
+    st = np.full((1, S, B), -1, np.int32)
+    st[0, ::2, 0], st[0, ::3, B - 1] = E - 1, 0
+    _compare(tr, E, B, st, policy=policy)
+    tr[0, S // 2, N // 2] = [E, 1]
+    tr[0, 0, N - 1] = [0, 0]
+    tr[0, S - 1, 0] = [-1, E + 3]
+    _compare(tr, E, B, st, policy=policy)
+    flat = torch.empty(tr.size + 1, dtype=torch.int32, device="cuda")
+    flat[1:] = torch.from_numpy(tr.reshape(-1))
+    g = L.maskmoe_cache_fetches(flat[1:].view(1, S, N, 2), E, B, policy=policy)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(g["fetches"].cpu().numpy(), C.cache_fetches(tr, E, B, policy=policy)[0])
