@@ -342,7 +342,8 @@ constexpr int kMaxSharedCombine = 8;   // the API's limit on shared experts
 // O values are loaded before any is added (same additions, same order). OB: O holds bf16
 // values (one slice); the sums are still formed in fp32. KC and OB together: a thread takes
 // eight columns (16-byte loads of every row, grid by kCombineColsOB).
-template <bool BF16, int KC = 0, bool OB = false>
+// SP (KC given, fp32 O): the most slices; every slice of every row is loaded before any is added.
+template <bool BF16, int KC = 0, bool OB = false, int SP = 1>
 __global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ Ov,
                                                        const int32_t* __restrict__ inv,
                                                        const float* __restrict__ gate, int T, int K,
@@ -401,10 +402,11 @@ __global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ O
   }
   const int nb = (d + kCombineCols - 1) / kCombineCols;
   const int t = blockIdx.x / nb, cb = blockIdx.x % nb;
-  if (BF16 && KC > 0) {  // d % 4 == 0, split == 1, K == KC, n_shared <= kMaxSharedCombine
+  if (BF16 && KC > 0) {  // d % 4 == 0, split <= SP, K == KC, n_shared <= kMaxSharedCombine
     const int c = cb * kCombineCols + threadIdx.x * 4;
     if (c >= d) return;
     constexpr int KA = KC > 0 ? KC : 1;   // array extent of the generic instance (branch not taken)
+    const size_t slice = static_cast<size_t>(T) * (KC + n_shared) * d;
     int row[KA];
     float gk[KA];
 #pragma unroll
@@ -412,23 +414,41 @@ __global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ O
       row[k] = inv[t * KC + k];
       gk[k] = gate[t * KC + k];
     }
-    float4 v[KA], vs[kMaxSharedCombine];
+    float4 v[KA][SP], vs[kMaxSharedCombine][SP];
 #pragma unroll
-    for (int k = 0; k < KC; ++k) v[k] = load_o4<OB>(Ov, static_cast<size_t>(row[k]) * d + c);
+    for (int k = 0; k < KC; ++k)
+#pragma unroll
+      for (int z = 0; z < SP; ++z)
+        if (z < split) v[k][z] = *reinterpret_cast<const float4*>(O + z * slice + static_cast<size_t>(row[k]) * d + c);
 #pragma unroll
     for (int sh = 0; sh < kMaxSharedCombine; ++sh)
       if (sh < n_shared)
-        vs[sh] = load_o4<OB>(Ov, (static_cast<size_t>(T) * KC + static_cast<size_t>(sh) * T + t) * d + c);
+#pragma unroll
+        for (int z = 0; z < SP; ++z)
+          if (z < split)
+            vs[sh][z] = *reinterpret_cast<const float4*>(
+                O + z * slice + (static_cast<size_t>(T) * KC + static_cast<size_t>(sh) * T + t) * d + c);
+    auto sum = [&](const float4 (&u)[SP]) {   // in slice order
+      float4 r = u[0];
+#pragma unroll
+      for (int z = 1; z < SP; ++z)
+        if (z < split) {
+          r.x += u[z].x; r.y += u[z].y; r.z += u[z].z; r.w += u[z].w;
+        }
+      return round_bf16x4(r);
+    };
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int k = 0; k < KC; ++k) {
-      s.x += gk[k] * v[k].x; s.y += gk[k] * v[k].y; s.z += gk[k] * v[k].z; s.w += gk[k] * v[k].w;
-      if (eo) *reinterpret_cast<float4*>(eo + (static_cast<size_t>(t) * KC + k) * d + c) = v[k];
+      const float4 o = sum(v[k]);
+      s.x += gk[k] * o.x; s.y += gk[k] * o.y; s.z += gk[k] * o.z; s.w += gk[k] * o.w;
+      if (eo) *reinterpret_cast<float4*>(eo + (static_cast<size_t>(t) * KC + k) * d + c) = o;
     }
 #pragma unroll
     for (int sh = 0; sh < kMaxSharedCombine; ++sh)
       if (sh < n_shared) {
-        s.x += vs[sh].x; s.y += vs[sh].y; s.z += vs[sh].z; s.w += vs[sh].w;
+        const float4 o = sum(vs[sh]);
+        s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
       }
     uint2 packed;
     packed.x = f32x2_to_bf16x2(s.x, s.y);
@@ -828,7 +848,12 @@ hipError_t launch_combine(const ExpertArgs& a, const PermBuffers& pb, const void
                           hipStream_t stream) {
   // bf16 O with K known: eight columns per thread
   const dim3 cgrid = combine_grid(a.T, a.d), cgrid8 = combine_grid(a.T, a.d, kCombineColsOB), cblk(256);
-  if (!ob)
+  // fp32 slices, K = 6: every row's slices loaded together (with two shared experts, 5 tokens: 7.8 us
+  // row by row, 4.6 together; K = 2 in eight slices gained nothing)
+  if (!ob && a.K == 6 && split <= 2)
+    hipLaunchKernelGGL((combine_kernel<true, 6, false, 2>), cgrid, cblk, 0, stream, O, pb.inv, a.gate, a.T, a.K,
+                       a.n_shared, a.d, y, split, a.expert_out);
+  else if (!ob)
     hipLaunchKernelGGL(combine_kernel<true>, cgrid, cblk, 0, stream, O, pb.inv, a.gate, a.T, a.K, a.n_shared, a.d, y,
                        split, a.expert_out);
   else if (a.K == 2)
