@@ -437,8 +437,8 @@ size_t maskmoe_layer_lora_workspace_bytes(const maskmoe_layer_desc* desc);
  * adapter).
  *
  *  lora       host pointer to the adapters; 1 <= rank <= 16, alpha finite.
- *  Other arguments as maskmoe_layer_forward; bf16 layers only, whatever T (the grouped-GEMM
- *  path).
+ *  Other arguments as maskmoe_layer_forward; bf16 layers only, whatever T (never the
+ *  few-token path).
  *  Rounding: A x, A h (fp32 sums) and (alpha / rank) B are rounded to bf16; each adapted
  *  product is then accumulated with W v in one fp32 sum; the rest as maskmoe_layer_forward.
  *  Errors: as maskmoe_layer_forward; E_INVAL for a NULL or misaligned adapter, a rank outside

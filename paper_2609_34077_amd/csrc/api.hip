@@ -314,7 +314,7 @@ static int layer_forward_impl(const maskmoe_layer_desc* desc, const void* x, con
     }
     skew = static_cast<float>(s1 * s1 / (s2 * d.E));
   }
-  const int batch_rows = bf16 && !train && !lora ? maskmoe::batch_tile_rows(d.T, d.K, pool, skew) : 0;
+  const int batch_rows = bf16 && !train && !decode ? maskmoe::batch_tile_rows(d.T, d.K, pool, skew) : 0;
   if (decode) {  // one workgroup routes every token and then permutes them
     e = maskmoe::launch_route_permute(x, w_router, d.T, d.d, d.E, d.K, d.route_mode, d.gate_mode, mask, prior, idx,
                                       gate, router_logits, d.n_shared, maskmoe::kGemmBM, pb, stream);
@@ -343,6 +343,23 @@ static int layer_forward_impl(const maskmoe_layer_desc* desc, const void* x, con
   a.expert_out = expert_out;
   a.T = d.T; a.d = d.d; a.F = d.F; a.E = d.E; a.K = d.K; a.n_shared = d.n_shared;
   a.packed = packed;
+  maskmoe::LoraArgs la{};
+  if (lora) {
+    la.rank = lora->rank;
+    la.scale = lora->alpha / static_cast<float>(lora->rank);
+    la.a_gate_up = static_cast<const uint16_t*>(lora->a_gate_up);
+    la.b_gate_up = static_cast<const uint16_t*>(lora->b_gate_up);
+    la.a_down = static_cast<const uint16_t*>(lora->a_down);
+    la.b_down = static_cast<const uint16_t*>(lora->b_down);
+    la.as_gate_up = static_cast<const uint16_t*>(lora->as_gate_up);
+    la.bs_gate_up = static_cast<const uint16_t*>(lora->bs_gate_up);
+    la.as_down = static_cast<const uint16_t*>(lora->as_down);
+    la.bs_down = static_cast<const uint16_t*>(lora->bs_down);
+    la.u = reinterpret_cast<uint16_t*>(ws + w.LU);
+    la.v = reinterpret_cast<uint16_t*>(ws + w.LV);
+    la.bp_gate_up = reinterpret_cast<uint16_t*>(ws + w.LBGU);
+    la.bp_down = reinterpret_cast<uint16_t*>(ws + w.LBD);
+  }
   if (!bf16) {
     e = maskmoe::launch_experts_f32(a, pb, reinterpret_cast<float*>(ws + w.H), reinterpret_cast<float*>(ws + w.O),
                                     y, stream, expert_marks);
@@ -353,29 +370,12 @@ static int layer_forward_impl(const maskmoe_layer_desc* desc, const void* x, con
   } else if (batch_rows) {
     e = maskmoe::launch_experts_batch(a, pb, batch_rows, pool, reinterpret_cast<uint16_t*>(ws + w.H),
                                       reinterpret_cast<uint16_t*>(ws + w.O), reinterpret_cast<float*>(ws + w.TP), y,
-                                      stream, expert_marks);
+                                      stream, expert_marks, lora ? &la : nullptr);
   } else {
     const int64_t TK = static_cast<int64_t>(d.T) * d.K;
     const int64_t nonempty = TK < d.E ? TK : d.E;
     const int64_t max_tiles = TK / maskmoe::kGemmBM + nonempty +
                               static_cast<int64_t>(d.n_shared) * ((d.T + maskmoe::kGemmBM - 1) / maskmoe::kGemmBM);
-    maskmoe::LoraArgs la{};
-    if (lora) {
-      la.rank = lora->rank;
-      la.scale = lora->alpha / static_cast<float>(lora->rank);
-      la.a_gate_up = static_cast<const uint16_t*>(lora->a_gate_up);
-      la.b_gate_up = static_cast<const uint16_t*>(lora->b_gate_up);
-      la.a_down = static_cast<const uint16_t*>(lora->a_down);
-      la.b_down = static_cast<const uint16_t*>(lora->b_down);
-      la.as_gate_up = static_cast<const uint16_t*>(lora->as_gate_up);
-      la.bs_gate_up = static_cast<const uint16_t*>(lora->bs_gate_up);
-      la.as_down = static_cast<const uint16_t*>(lora->as_down);
-      la.bs_down = static_cast<const uint16_t*>(lora->bs_down);
-      la.u = reinterpret_cast<uint16_t*>(ws + w.LU);
-      la.v = reinterpret_cast<uint16_t*>(ws + w.LV);
-      la.bp_gate_up = reinterpret_cast<uint16_t*>(ws + w.LBGU);
-      la.bp_down = reinterpret_cast<uint16_t*>(ws + w.LBD);
-    }
     e = maskmoe::launch_experts_bf16(a, pb, reinterpret_cast<uint16_t*>(ws + w.H),
                                      reinterpret_cast<float*>(ws + w.O), reinterpret_cast<float*>(ws + w.TP), y,
                                      static_cast<int>(max_tiles), stream,

@@ -16,6 +16,7 @@
 // gate/up 189 -> 145 us, down 131 -> 83 us. Three or four chunks in flight changed nothing, and
 // 256 token rows (one workgroup per CU) lost 15-60%: its loads, LDS accesses and products no
 // longer overlap.
+// Adapted experts (LORA) take the adapters' term as one more chunk, as the many-token path does.
 // The down projection splits its reduction when the tiles alone would leave the chip idle; its
 // fp32 slices are added, in order, by the combine.
 
@@ -45,6 +46,8 @@ struct BatchArgs {
   uint16_t* out;            // EPI 0: H [rows, F]; EPI 1: O [rows, d]
   float* part;              // EPI 1 with split > 1: [split, rows, d] fp32
   int G, E, N, K, F, rows;  // N: output columns (F or d), K: reduction length
+  const uint16_t* lora_u;   // LORA: rank projections of a's rows, bf16 [rows, 64]
+  const uint16_t* lora_b;   // LORA: the scaled adapter rows beside the weight rows, bf16 [G, weight rows, 64]
   int n_tiles, split, a_rows;   // a_rows: rows of a (T or rows)
 };
 
@@ -55,12 +58,15 @@ constexpr int kPieces = kPW + BM / kRowsPerPiece;
 
 // The stream of one tile: acc += W X^T over nc chunks. off[]: this thread's 16-byte pieces of a
 // chunk (the first PW are weights, in w from byte w0 + chunk * wstep; then tokens, in a from a0 + 128 chunk).
-// rot: the chunk to start with. NT: non-temporal weight loads.
-template <int BM, bool NT>
+// rot: the chunk to start with. NT: non-temporal weight loads. LORA: with `extra`, one more chunk goes
+// first, the adapters' term [s B] U^T (weight pieces in xw at xoff[], token pieces in xu).
+template <int BM, bool NT, bool LORA>
 __device__ __forceinline__ void stream_tile(const void* w, uint32_t wbytes, uint32_t w0, uint32_t wstep,
                                             const void* a, uint32_t abytes, uint32_t a0, int nc, int rot,
                                             const uint32_t (&off)[kPieces<BM>], u32x4 (*lds)[(kW + BM) * 8], int wrow0,
-                                            int wrow1, int trow, f32x16 (&acc)[2][BM / 64]) {
+                                            int wrow1, int trow, f32x16 (&acc)[2][BM / 64], bool extra,
+                                            const void* xw, uint32_t xwbytes, const void* xu, uint32_t xubytes,
+                                            const uint32_t (&xoff)[kPieces<BM>]) {
   constexpr int TN = BM / 64, PER = kPieces<BM>;
   const int tid = threadIdx.x, lane = tid & 63;
   const int dst = (tid >> 3) * 8 + ((tid & 7) ^ lds_swizzle(tid >> 3));   // piece i: + kThreads * i
@@ -69,7 +75,9 @@ __device__ __forceinline__ void stream_tile(const void* w, uint32_t wbytes, uint
   // Past the last chunk the buffers are empty: the loads return zeros without touching memory,
   // and every step has the same loads behind the ones its stores wait for.
   constexpr int kNt = 2;   // the load's non-temporal bit
-  auto load = [&](int c, u32x4 (&r)[PER]) {
+  const int x = LORA && extra ? 1 : 0, steps = nc + x;
+  auto load = [&](int ci, u32x4 (&r)[PER]) {
+    const int c = LORA ? ci - x : ci;
     const __amdgpu_buffer_rsrc_t wr = make_rsrc(w, c < nc ? wbytes : 0), ar = make_rsrc(a, c < nc ? abytes : 0);
     const int rc = c + rot >= nc ? c + rot - nc : c + rot;   // walks the chunks from `rot` around
     const uint32_t ws = w0 + static_cast<uint32_t>(rc) * wstep, as = a0 + static_cast<uint32_t>(rc) * (2 * kCK);
@@ -107,9 +115,15 @@ __device__ __forceinline__ void stream_tile(const void* w, uint32_t wbytes, uint
     __builtin_amdgcn_sched_barrier(0);
     store(buf ^ 1, reg[buf ^ 1]);
     lds_sync();
-    return ++c < nc;
+    return ++c < steps;
   };
-  load(0, reg[0]);
+  if (LORA && extra) {
+    const __amdgpu_buffer_rsrc_t br = make_rsrc(xw, xwbytes), ur = make_rsrc(xu, xubytes);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) reg[0][i] = __builtin_amdgcn_raw_buffer_load_b128(i < kPW ? br : ur, xoff[i], 0, 0);
+  } else {
+    load(0, reg[0]);
+  }
   load(1, reg[1]);
   store(0, reg[0]);
   lds_sync();
@@ -118,7 +132,7 @@ __device__ __forceinline__ void stream_tile(const void* w, uint32_t wbytes, uint
 }
 
 // EPI 0: gate/up with SwiGLU; EPI 1: down. PACKED: weights in the packed layout.
-template <int EPI, int BM, bool PACKED>
+template <int EPI, int BM, bool PACKED, bool LORA>
 __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void batch_gemm_kernel(const BatchArgs p) {
   constexpr int TN = BM / 64;                  // 32-token fragments per wavefront
   __shared__ u32x4 lds[2][(kW + BM) * 8];
@@ -189,10 +203,31 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void batch_gemm_kernel(
   // not all read the same columns of the token and weight rows at once (1 to 3% of a layer:
   // Mixtral-shaped, 400 tokens, plain, 584 -> 573 us; DeepSeek-shaped, 700, row-major, 311 -> 304).
   const int rot = nt * 13 % nc;
+  // the adapters' chunk, in the first slice: weight rows of lora_b, token rows of U
+  const bool extra = LORA && z == 0;
+  uint32_t xoff[kPieces<BM>];
+  const void* xw = nullptr;
+  const uint32_t wrows = EPI == 0 ? 2 * p.F : p.N;
+  if (LORA) {
+    xw = p.lora_b + static_cast<size_t>(g) * wrows * 64;
+#pragma unroll
+    for (int i = 0; i < kPieces<BM>; ++i) {
+      if (i < kPW) {
+        const int r = kRowsPerPiece * i + pr;
+        const int row = EPI == 0 ? (r < kW / 2 ? n0 + r : p.F + n0 + r - kW / 2) : min(n0 + r, p.N - 1);
+        xoff[i] = static_cast<uint32_t>(row * 64 + pc * 8) * 2u;
+      } else {
+        const int r = row0 + kRowsPerPiece * (i - kPW) + pr;
+        xoff[i] = r < row_end ? static_cast<uint32_t>(r * 64 + pc * 8) * 2u : kNoRow;
+      }
+    }
+  }
   if (mtiles == 1)
-    stream_tile<BM, true>(wg, wbytes, w0, wstep, p.a, abytes, a0, nc, rot, off, lds, wrow0, wrow1, trow, acc);
+    stream_tile<BM, true, LORA>(wg, wbytes, w0, wstep, p.a, abytes, a0, nc, rot, off, lds, wrow0, wrow1, trow, acc, extra, xw, wrows * 128u, p.lora_u,
+                                static_cast<uint32_t>(p.rows) * 128u, xoff);
   else
-    stream_tile<BM, false>(wg, wbytes, w0, wstep, p.a, abytes, a0, nc, rot, off, lds, wrow0, wrow1, trow, acc);
+    stream_tile<BM, false, LORA>(wg, wbytes, w0, wstep, p.a, abytes, a0, nc, rot, off, lds, wrow0, wrow1, trow, acc, extra, xw, wrows * 128u, p.lora_u,
+                                static_cast<uint32_t>(p.rows) * 128u, xoff);
 
   // acc[i][j][4 q + e]: weight row 8 q + 4 (lane >> 5) + e of fragment i, token row lane & 31 of
   // fragment j
@@ -236,8 +271,14 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void batch_gemm_kernel(
 
 template <int EPI, int BM>
 void launch_bm(bool packed, int grid, const BatchArgs& p, hipStream_t s) {
-  if (packed) hipLaunchKernelGGL((batch_gemm_kernel<EPI, BM, true>), dim3(grid), dim3(kThreads), 0, s, p);
-  else hipLaunchKernelGGL((batch_gemm_kernel<EPI, BM, false>), dim3(grid), dim3(kThreads), 0, s, p);
+  const dim3 g(grid), b(kThreads);
+  if (p.lora_b) {
+    if (packed) hipLaunchKernelGGL((batch_gemm_kernel<EPI, BM, true, true>), g, b, 0, s, p);
+    else hipLaunchKernelGGL((batch_gemm_kernel<EPI, BM, false, true>), g, b, 0, s, p);
+  } else {
+    if (packed) hipLaunchKernelGGL((batch_gemm_kernel<EPI, BM, true, false>), g, b, 0, s, p);
+    else hipLaunchKernelGGL((batch_gemm_kernel<EPI, BM, false, false>), g, b, 0, s, p);
+  }
 }
 
 template <int EPI>
@@ -260,7 +301,6 @@ hipError_t launch(int bm, bool packed, int grid, const BatchArgs& p, hipStream_t
 // path's tiles are never full, and the line lies later: DeepSeek-shaped, soft, 112 rows
 // 396 / 354 / 399, 159 rows 483 / 424 / 409.
 int batch_tile_rows(int T, int K, int pool, float skew) {
-  if (T <= kDecodeMaxT) return 0;
   const double avg = static_cast<double>(T) * K / pool;
   if (avg <= 30) return 64;
   return (pool >= 32 ? avg <= 112 : avg <= 104 * skew) ? 128 : 0;
@@ -280,7 +320,7 @@ static int batch_split(int tiles, int rows, int d, int F) {
 }
 
 hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int bm, int pool, uint16_t* H, uint16_t* O,
-                                float* part, void* y, hipStream_t stream, hipEvent_t* marks) {
+                                float* part, void* y, hipStream_t stream, hipEvent_t* marks, const LoraArgs* lora) {
   const int64_t TK = static_cast<int64_t>(a.T) * a.K;
   const int nonempty = static_cast<int>(std::min<int64_t>(TK, a.E));
   const int shared_tiles = a.n_shared * ((a.T + bm - 1) / bm);
@@ -299,9 +339,22 @@ hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int 
   p.N = a.F; p.K = a.d; p.a_rows = a.T;
   p.n_tiles = a.F / (kW / 2);
   p.split = 1;
-  hipError_t err = launch<0>(bm, a.packed, max_tiles * p.n_tiles, p, stream);
+  hipError_t err;
+  if (lora) {
+    err = launch_lora_prepare(*lora, a, pb, bm, max_tiles, stream);
+    if (err != hipSuccess) return err;
+    p.lora_u = lora->u;
+    p.lora_b = lora->bp_gate_up;
+  }
+  err = launch<0>(bm, a.packed, max_tiles * p.n_tiles, p, stream);
   if (err != hipSuccess) return err;
   record_mark(marks, 0, stream);
+  if (lora) {
+    err = launch_lora_hidden(*lora, a, pb, bm, max_tiles, H, stream);
+    if (err != hipSuccess) return err;
+    p.lora_u = lora->v;
+    p.lora_b = lora->bp_down;
+  }
 
   p.a = H;
   p.w = static_cast<const uint16_t*>(a.w_down);

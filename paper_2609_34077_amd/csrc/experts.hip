@@ -885,10 +885,7 @@ hipError_t launch_experts_bf16(const ExpertArgs& a, const PermBuffers& pb, uint1
   const dim3 fixup_grid(8 * kTailSlotsPerXcd * kTailFixParts);
   hipError_t err;
   if (lora) {
-    err = launch_lora_pack(*lora, G, a.E, a.F, a.d, stream);
-    if (err != hipSuccess) return err;
-    err = launch_lora_down(static_cast<const uint16_t*>(a.x), pb.row_tok, a.d, lora->a_gate_up,
-                           lora->as_gate_up, 2 * lora->rank, G, a.E, pb, max_tiles, lora->u, stream);
+    err = launch_lora_prepare(*lora, a, pb, kGemmBM, max_tiles, stream);
     if (err != hipSuccess) return err;
     g.lora_u = lora->u;
     g.lora_b = lora->bp_gate_up;
@@ -910,8 +907,7 @@ hipError_t launch_experts_bf16(const ExpertArgs& a, const PermBuffers& pb, uint1
   if (err != hipSuccess) return err;
   record_mark(marks, 0, stream);
   if (lora) {
-    err = launch_lora_down(H, nullptr, a.F, lora->a_down, lora->as_down, lora->rank, G, a.E, pb, max_tiles, lora->v,
-                           stream);
+    err = launch_lora_hidden(*lora, a, pb, kGemmBM, max_tiles, H, stream);
     if (err != hipSuccess) return err;
     g.lora_u = lora->v;
     g.lora_b = lora->bp_down;

@@ -111,12 +111,13 @@ struct LoraArgs {
   const uint16_t *as_gate_up, *bs_gate_up, *as_down, *bs_down;
   uint16_t *u, *v, *bp_gate_up, *bp_down;
 };
-hipError_t launch_lora_pack(const LoraArgs& l, int G, int E, int F, int d, hipStream_t stream);
-// out [rows, 64] = src rows (gathered through row_tok when given) times the rows' group adapter
-// A [nq, K]^T, zero-padded; rows tiled as the permutation (kGemmBM rows per tile).
-hipError_t launch_lora_down(const uint16_t* src, const int32_t* row_tok, int K, const uint16_t* a, const uint16_t* as,
-                            int nq, int G, int E, const PermBuffers& pb, int max_tiles, uint16_t* out,
-                            hipStream_t stream);
+// Both scaled, padded B matrices and u [rows, 64] = rows of x (gathered through row_tok) times their
+// group's A^T, zero-padded; then v from the SwiGLU rows h. Rows tiled as the permutation (tile_rows, a
+// multiple of 16; at most max_tiles tiles).
+hipError_t launch_lora_prepare(const LoraArgs& l, const ExpertArgs& a, const PermBuffers& pb, int tile_rows,
+                               int max_tiles, hipStream_t stream);
+hipError_t launch_lora_hidden(const LoraArgs& l, const ExpertArgs& a, const PermBuffers& pb, int tile_rows,
+                              int max_tiles, const uint16_t* h, hipStream_t stream);
 
 // Partial-tile slots of the grouped GEMMs' split tail tiles (fp32 256 x 256 each, 64 MiB).
 // Workgroups one XCD of the current device runs at once (one 256 x 256 tile per CU, the CUs
@@ -143,14 +144,15 @@ int decode_split(int T, int d, int F, int E, int K, int n_shared);
 int decode_split_gate_up(int T, int d, int F, int E, int K, int n_shared);
 hipError_t launch_experts_bf16_decode(const ExpertArgs& a, const PermBuffers& pb, uint16_t* H, float* P, float* O,
                                       void* y, hipStream_t stream, hipEvent_t* marks);
-// bf16, a serving-sized batch (batch.hip): tokens above kDecodeMaxT but few enough rows per
-// expert that the weight stream bounds the layer. batch_tile_rows: the row-tile size to permute
+// bf16, a serving-sized batch (batch.hip): few enough rows per expert that the weight stream bounds the
+// layer (with adapters for any number of tokens, else above kDecodeMaxT). batch_tile_rows: the row-tile size to permute
 // and launch with, 0 when the many-token path is faster; pool: experts the routing can select,
 // skew: 1, or with a soft prior the smaller share of them that it concentrates on.
 // O: bf16 expert outputs [rows, d]; part: kTailPartBytes for the down projection's slices.
 int batch_tile_rows(int T, int K, int pool, float skew);
 hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int bm, int pool, uint16_t* H, uint16_t* O,
-                                float* part, void* y, hipStream_t stream, hipEvent_t* marks);
+                                float* part, void* y, hipStream_t stream, hipEvent_t* marks,
+                                const LoraArgs* lora = nullptr);
 // y = the gate-weighted combine of a bf16 layer's expert outputs: O [rows, d] bf16 (ob), or fp32
 // slices [split, rows, d].
 hipError_t launch_combine(const ExpertArgs& a, const PermBuffers& pb, const void* O, bool ob, int split, void* y,

@@ -10,6 +10,7 @@ import pytest
 from paper_2609_34077_amd import _lib as L
 from paper_2609_34077_amd import synth
 from test_gpu_layer import check_layer
+from test_gpu_lora import check_lora
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +44,11 @@ def test_batch_rows(cfg):
 @pytest.mark.parametrize("cfg", [c for c in CASES if c.d % 128 == 0], ids=lambda c: c.name)
 def test_batch_packed(cfg):
     check_layer(cfg, packed=True)
+
+
+# the adapters' chunk in front of the weight chunks: 64- and 128-row tiles, a split reduction (only
+# its first slice takes the adapters), ragged weight rows, one token
+@pytest.mark.parametrize("T,E,K,ns,d,F,rank", [(1, 8, 2, 1, 64, 64, 8), (17, 8, 2, 0, 128, 2048, 16), (129, 8, 2, 1, 192, 320, 4),
+                                               (300, 64, 6, 2, 256, 192, 8)])
+def test_batch_lora(T, E, K, ns, d, F, rank):
+    check_lora(_cfg(T, E, K, ns, d, F), rank=rank)
