@@ -301,20 +301,20 @@ static int layer_forward_impl(const maskmoe_layer_desc* desc, const void* x, con
   // Training always takes the grouped-GEMM path, whose gate/up epilogue can keep the
   // pre-activations for the backward.
   const bool decode = uses_decode_path(d) && !train && !lora;
-  int pool = d.E;   // experts that the routing can select, and how evenly the prior weighs them
-  float skew = 1.0f;
+  int pool = d.E;      // experts that the routing can select
+  float peak = 1.0f;   // the prior's largest entry over a uniform one's
   if (d.route_mode == MASKMOE_ROUTE_HARD_MASK) {
     pool = 0;
     for (int i = 0; i < d.E; ++i) pool += mask[i] != 0;
   } else if (d.route_mode == MASKMOE_ROUTE_SOFT_PRIOR) {
-    double s1 = 0.0, s2 = 0.0;
+    double sum = 0.0, top = 0.0;
     for (int i = 0; i < d.E; ++i) {
-      s1 += prior[i];
-      s2 += static_cast<double>(prior[i]) * prior[i];
+      sum += prior[i];
+      if (prior[i] > top) top = prior[i];
     }
-    skew = static_cast<float>(s1 * s1 / (s2 * d.E));
+    peak = static_cast<float>(top * d.E / sum);
   }
-  const int batch_rows = bf16 && !train && !decode ? maskmoe::batch_tile_rows(d.T, d.K, pool, skew) : 0;
+  const int batch_rows = bf16 && !train && !decode ? maskmoe::batch_tile_rows(d.T, d.K, pool, peak) : 0;
   if (decode) {  // one workgroup routes every token and then permutes them
     e = maskmoe::launch_route_permute(x, w_router, d.T, d.d, d.E, d.K, d.route_mode, d.gate_mode, mask, prior, idx,
                                       gate, router_logits, d.n_shared, maskmoe::kGemmBM, pb, stream);

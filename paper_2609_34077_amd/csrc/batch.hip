@@ -290,20 +290,22 @@ hipError_t launch(int bm, bool packed, int grid, const BatchArgs& p, hipStream_t
 
 }  // namespace
 
-// By the rows an expert gets on average, since the time goes with the passes over the weights
-// (row tiles). Layer times with 64-row, 128-row and the many-token path's 256-row tiles:
-// Mixtral-shaped, plain routing, 30 rows 488 / 500 / 661 us, 64 rows 613 / 557 / 661, 100 rows
-// 718 / 608 / 674, 128 rows 837 / 788 / 682; hard mask over 4 experts, 30 rows 271 / 281 / 365,
-// 100 rows 377 / 337 / 366, 128 rows 434 / 427 / 366. A soft prior sends more rows to some
-// experts: `skew` is the share of them (1 / (E sum pi^2) with sum pi = 1) that a uniform
-// routing with the same concentration would use; soft prior over 4 of 8 experts, 91 rows on
-// that count 633 / 605 / 664, 106 rows 706 / 679 / 664. With dozens of experts the many-token
-// path's tiles are never full, and the line lies later: DeepSeek-shaped, soft, 112 rows
-// 396 / 354 / 399, 159 rows 483 / 424 / 409.
-int batch_tile_rows(int T, int K, int pool, float skew) {
+// By the rows an expert gets, since the time goes with the passes over the weights (row tiles).
+// Layer times with 64-row and 128-row tiles here and on the many-token path (256-row tiles whose
+// last one multiplies only its own 64-row pieces), by the average rows of a selectable expert:
+// Mixtral-shaped, plain routing, 24 rows 448 / 461 / 585 us, 75 rows 742 / 539 / 576, 100 rows
+// 705 / 574 / 585, 150 rows 957 / 955 / 625; hard mask over 4 experts, 75 rows 362 / 286 / 322,
+// 150 rows 485 / 488 / 339. A prior sends more rows to some experts, whose second 128-row tile is
+// another pass over their weights: `peak` is its largest entry over a uniform one's; soft prior
+// over 4 of 8 experts (peak 1.5), 50 rows 580 / 522 / 594, 75 rows 664 / 635 / 594. With dozens
+// of experts the tiles of neighbouring experts hide such passes and the line lies at the average:
+// DeepSeek-shaped, soft (peak 2.1), 31 rows 240 / 249 / 276, 66 rows 302 / 286 / 303, 94 rows
+// 360 / 329 / 317, 113 rows 396 / 354 / 328; over its 12-expert set, 32 rows 82 / 87 / 84, 100
+// rows 96 / 97 / 100, 200 rows 138 / 125 / 107.
+int batch_tile_rows(int T, int K, int pool, float peak) {
   const double avg = static_cast<double>(T) * K / pool;
-  if (avg <= 30) return 64;
-  return (pool >= 32 ? avg <= 112 : avg <= 104 * skew) ? 128 : 0;
+  if (avg <= 36) return 64;
+  return (pool >= 32 ? avg <= 85 : avg * peak <= 104) ? 128 : 0;
 }
 
 // Slices of the down projection's reduction: up to about 600 workgroups, 16 chunks a slice.

@@ -75,16 +75,16 @@ __device__ __forceinline__ int find_group(const int32_t* tile_off, int G, int mt
 // Epilogue of a finished tile: rows [row0, row_end) of one group, columns from n0. EPI 0:
 // SwiGLU of the gate / up column pairs into H (bf16; the pre-activations into ab when given);
 // EPI 1: O, each expert output rounded to bf16 (the layer's dtype; the combine adds them in
-// fp32). acc[i][j][4*jj+ii] is row wm*128 + i*32 + 8*jj + 4*(lane>>5) + ii, column (lane & 31)
+// fp32). acc[i][j][4*jj+ii] is row wm*32*TM + i*32 + 8*jj + 4*(lane>>5) + ii, column (lane & 31)
 // of fragment j. The bf16 tile is staged in LDS (free after the k-loop; rows padded by 16
 // bytes, conflict-free) and stored eight columns per 16-byte access: a lane holds one column
 // of each row it owns, and 2-byte stores kept the texture-address path busy for several
 // percent of a tile.
-template <int COLS>   // columns of the staged tile: LDS row pitch COLS + 8 elements
+template <int COLS, int ROWS>   // the staged tile; LDS row pitch COLS + 8 elements
 __device__ __forceinline__ void store_staged(const uint16_t* stg, uint16_t* out, size_t ld, int row0, int row_end,
                                              int col0, int ncol) {
   constexpr int G = COLS / 8;   // 8-column groups per row
-  for (int u = threadIdx.x; u < 256 * G; u += kTileThreads) {
+  for (int u = threadIdx.x; u < ROWS * G; u += kTileThreads) {
     const int lr = u / G, cg = (u % G) * 8;
     const int row = row0 + lr, col = col0 + cg;
     if (row >= row_end || col >= ncol) continue;
@@ -98,19 +98,19 @@ __device__ __forceinline__ void store_staged(const uint16_t* stg, uint16_t* out,
   }
 }
 
-template <int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, const f32x16 (&acc)[kTileTM][kTileTN], int row0,
+template <int EPI, int TM>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, const f32x16 (&acc)[TM][kTileTN], int row0,
                                               int row_end, int n0, TileLds& L) {
-  constexpr int WN = 4, TM = kTileTM, TN = kTileTN;
+  constexpr int WN = 4, TN = kTileTN, ROWS = 64 * TM;
   constexpr int COLS = EPI == 0 ? BN / 2 : BN, PITCH = COLS + 8;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / WN, wn = wave % WN;
   uint16_t* stg = reinterpret_cast<uint16_t*>(&L);
-  static_assert((EPI == 0 ? 2 : 1) * 256 * PITCH * 2 <= sizeof(TileLds), "the staged tiles fit in LDS");
+  static_assert((EPI == 0 ? 2 : 1) * ROWS * PITCH * 2 <= sizeof(TileLds), "the staged tiles fit in LDS");
   wait_lgkmcnt0();
   tile_barrier();   // every wave is past the k-loop's LDS reads and DMA writes
   // this lane's rows of the tile: row_of(i, r)
-  auto row_of = [&](int i, int r) { return wm * 128 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
+  auto row_of = [&](int i, int r) { return wm * 32 * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
   if (EPI == 0) {   // H, and the gate pre-activations when kept (the up ones follow)
     const int c = wn * 32 + (lane & 31);
 #pragma unroll
@@ -121,7 +121,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, const f32x16 (&
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) stg[256 * PITCH + row_of(i, r) * PITCH + c] = f32_to_bf16(acc[i][0][r]);
+        for (int r = 0; r < 16; ++r) stg[ROWS * PITCH + row_of(i, r) * PITCH + c] = f32_to_bf16(acc[i][0][r]);
   } else {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -134,9 +134,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, const f32x16 (&
   tile_barrier();
   uint16_t* out = static_cast<uint16_t*>(p.out);
   if (EPI == 0) {
-    store_staged<COLS>(stg, out, p.F, row0, row_end, n0, p.F);
+    store_staged<COLS, ROWS>(stg, out, p.F, row0, row_end, n0, p.F);
     if (p.ab) {
-      store_staged<COLS>(stg + 256 * PITCH, p.ab, 2 * static_cast<size_t>(p.F), row0, row_end, n0, p.F);
+      store_staged<COLS, ROWS>(stg + ROWS * PITCH, p.ab, 2 * static_cast<size_t>(p.F), row0, row_end, n0, p.F);
       wait_lgkmcnt0();
       tile_barrier();   // the staged tiles are read: stage the up pre-activations
 #pragma unroll
@@ -145,18 +145,22 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, const f32x16 (&
         for (int r = 0; r < 16; ++r) stg[row_of(i, r) * PITCH + wn * 32 + (lane & 31)] = f32_to_bf16(acc[i][1][r]);
       wait_lgkmcnt0();
       tile_barrier();
-      store_staged<COLS>(stg, p.ab + p.F, 2 * static_cast<size_t>(p.F), row0, row_end, n0, p.F);
+      store_staged<COLS, ROWS>(stg, p.ab + p.F, 2 * static_cast<size_t>(p.F), row0, row_end, n0, p.F);
     }
   } else {
-    store_staged<COLS>(stg, out, p.d, row0, row_end, n0, p.d);
+    store_staged<COLS, ROWS>(stg, out, p.d, row0, row_end, n0, p.d);
   }
 }
 
+// A group's last row tile multiplies (and loads) only its 64-row pieces that hold rows, the two wave
+// groups sharing them evenly: 256-row tiles of a DeepSeek-shaped batch of 2000 tokens are a third
+// padding. Layers at 2000 tokens: DeepSeek-shaped, soft prior 488 -> 401 us (with adapters
+// 556 -> 476), 1000 tokens 386 -> 317; Mixtral-shaped, 400 tokens 664 -> 592.
 // PACKED: the expert matrices are in the packed layout (kPackRows x kPackCols blocks).
 template <int EPI, bool LORA = false, bool PACKED = false>
 __global__ __launch_bounds__(GEMM_THREADS) void grouped_gemm_bf16(const GemmArgs p) {
   constexpr int WN = 4;                 // waves: 2 along rows x 4 along columns
-  constexpr int TM = kTileTM, TN = kTileTN;
+  constexpr int TN = kTileTN;
   __shared__ TileLds lds;
 
   // The grid covers the most tiles any routing can need plus the tail slices; tile_job gives
@@ -176,11 +180,12 @@ __global__ __launch_bounds__(GEMM_THREADS) void grouped_gemm_bf16(const GemmArgs
   const int n0 = nt * (EPI == 0 ? BN / 2 : BN);
   const int nks = Kdim / BK / job.s;   // k-tiles of this slice
   const int k0 = z * nks * BK;
+  const int tm = job.s > 1 ? kTileTM : min((row_end - row0 + 63) / 64, kTileTM);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wn = wave % WN;
 
-  // This lane's four rows of the A and B tiles (tile_dma_row in gemm_tile.hpp). B tile rows
+  // This lane's rows of the A and B tiles (tile_dma_row_a, tile_dma_row in gemm_tile.hpp). B tile rows
   // 0..127 of the gate/up GEMM are W_gate rows n0.., rows 128..255 the matching W_up rows.
   const uint16_t* wg = g < p.E ? p.w + static_cast<size_t>(g) * (EPI == 0 ? 2 * p.F : p.d) * Kdim
                                : p.ws + static_cast<size_t>(g - p.E) * (EPI == 0 ? 2 * p.F : p.d) * Kdim;
@@ -193,8 +198,8 @@ __global__ __launch_bounds__(GEMM_THREADS) void grouped_gemm_bf16(const GemmArgs
   for (int i = 0; i < 4; ++i) {
     const int r = tile_dma_row(i);
     const int chunk = tile_dma_chunk(i) * 8;
-    const int row = min(row0 + r, row_end - 1);
-    ops.aoff[i] = static_cast<uint32_t>((EPI == 0 ? p.row_tok[row] : row) * Kdim + chunk) * 2u;
+    const int row = min(row0 + tile_dma_row_a(tm, i), row_end - 1);
+    ops.aoff[i] = static_cast<uint32_t>((EPI == 0 ? p.row_tok[row] : row) * Kdim + tile_dma_chunk_a(tm, i) * 8) * 2u;
     int brow, grp, rig;   // row in the matrix; its packed group and row within the group
     if (EPI == 0) {
       const int n = min(n0 + (r & 127), p.F - 1);
@@ -216,33 +221,42 @@ __global__ __launch_bounds__(GEMM_THREADS) void grouped_gemm_bf16(const GemmArgs
 #pragma unroll
   for (int j = 0; j < TN; ++j) bfrag[j] = (EPI == 0 ? (j == 0 ? 0 : 128) + wn * 32 : wn * 64 + j * 32) + (lane & 31);
 
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-  if (LORA && z == 0) {   // the adapters' term as one more k-tile: A' = [U | rows], B' = [s B | W]
-    TileOps ex;
+  TileOps ex;
+  const bool extra = LORA && z == 0;   // the adapters' term as one more k-tile: A' = [U | rows], B' = [s B | W]
+  if (extra) {
     ex.a = reinterpret_cast<const char*>(p.lora_u);
     ex.b = reinterpret_cast<const char*>(p.lora_b + static_cast<size_t>(g) * (EPI == 0 ? 2 * p.F : p.d) * 64);
     ex.b_step = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int chunk = tile_dma_chunk(i) * 8;
-      ex.aoff[i] = static_cast<uint32_t>(min(row0 + tile_dma_row(i), row_end - 1) * 64 + chunk) * 2u;
-      ex.boff[i] = static_cast<uint32_t>(brows[i] * 64 + chunk) * 2u;
+      ex.aoff[i] =
+          static_cast<uint32_t>(min(row0 + tile_dma_row_a(tm, i), row_end - 1) * 64 + tile_dma_chunk_a(tm, i) * 8) * 2u;
+      ex.boff[i] = static_cast<uint32_t>(brows[i] * 64 + tile_dma_chunk(i) * 8) * 2u;
     }
-    gemm_tile_mainloop<true>(ops, nks, bfrag, acc, lds, &ex);
-  } else {
-    gemm_tile_mainloop<false>(ops, nks, bfrag, acc, lds);
   }
-  if (job.s > 1) {   // a slice of a split tail tile: its partial tile goes to the slot
-    tail_store_partial(p.part, job.slot, acc);
-    return;
-  }
-  gemm_epilogue<EPI>(p, acc, row0, row_end, n0, lds);
+  auto tile = [&](auto tm_c) {
+    constexpr int TM = decltype(tm_c)::value;
+    f32x16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    if (extra) gemm_tile_mainloop<true, false, false, false, TM>(ops, nks, bfrag, acc, lds, &ex);
+    else gemm_tile_mainloop<false, false, false, false, TM>(ops, nks, bfrag, acc, lds);
+    if constexpr (TM == kTileTM) {
+      if (job.s > 1) {   // a slice of a split tail tile: its partial tile goes to the slot
+        tail_store_partial(p.part, job.slot, acc);
+        return;
+      }
+    }
+    gemm_epilogue<EPI, TM>(p, acc, row0, row_end, n0, lds);
+  };
+  if (tm == 4) tile(std::integral_constant<int, 4>{});
+  else if (tm == 3) tile(std::integral_constant<int, 3>{});
+  else if (tm == 2) tile(std::integral_constant<int, 2>{});
+  else tile(std::integral_constant<int, 1>{});
 }
 
 // Adds the slices of each split tail tile of the down GEMM (grouped_gemm_bf16<1>) in slice order

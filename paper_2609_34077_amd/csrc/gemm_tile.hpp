@@ -37,6 +37,15 @@ __device__ __forceinline__ int tile_dma_row(int i) {
   return (wave >> 2) * 128 + 8 * (4 * (wave & 3) + i) + ((threadIdx.x & 63) >> 3);
 }
 __device__ __forceinline__ int tile_dma_chunk(int i) { return (threadIdx.x & 7) ^ lds_swizzle(tile_dma_row(i)); }
+// The same for the A operand of a tile of 64 tm rows (tm fragments per wave, i < tm): group g's
+// rows are 32 tm g .. 32 tm (g + 1) - 1.
+__device__ __forceinline__ int tile_dma_row_a(int tm, int i) {
+  const int wave = threadIdx.x >> 6;
+  return (wave >> 2) * 32 * tm + 8 * (tm * (wave & 3) + i) + ((threadIdx.x & 63) >> 3);
+}
+__device__ __forceinline__ int tile_dma_chunk_a(int tm, int i) {
+  return (threadIdx.x & 7) ^ lds_swizzle(tile_dma_row_a(tm, i));
+}
 
 // Operands of one tile: byte bases at the first k-tile (wave-uniform) and this lane's byte
 // offsets of its four rows (tile_dma_row(i), chunk included) of each; A k-tiles are 128 bytes
@@ -133,19 +142,22 @@ __device__ __forceinline__ void tile_barrier() { asm volatile("s_barrier" ::: "m
 // matching TileOps fields are unused). bfrag[j]: tile row of B fragment j for this lane (a
 // multiple of 32 plus lane & 31); A fragment i is tile row 128 g + 32 i + (lane & 31).
 // STREAM: operand B is read by this workgroup alone: non-temporal loads.
-template <bool EXTRA = false, bool AKM = false, bool BKM = false, bool STREAM = false>
+// TM: A fragments per wave; a tile of 64 TM rows, A fragment i then being tile row
+// 32 TM g + 32 i + (lane & 31) and o.aoff / o.x's following tile_dma_row_a(TM, i).
+template <bool EXTRA = false, bool AKM = false, bool BKM = false, bool STREAM = false, int TM = kTileTM>
 __device__ __forceinline__ void gemm_tile_mainloop(const TileOps& o, int nk, const int (&bfrag)[kTileTN],
-                                                   f32x16 (&acc)[kTileTM][kTileTN], TileLds& L,
+                                                   f32x16 (&acc)[TM][kTileTN], TileLds& L,
                                                    const TileOps* x = nullptr, const TileKm* akm = nullptr,
                                                    const TileKm* bkm = nullptr) {
   static_assert(!(EXTRA && (AKM || BKM)), "the extra k-tile is K-contiguous");
+  static_assert(!AKM || TM == kTileTM, "a K-major A operand fills the tile");
   constexpr int X = EXTRA ? 1 : 0;
   if (nk <= 0) return;
   const int ntot = nk + X;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int g = wave >> 2, q = wave & 3;
-  const uint32_t la0 = lds_offset(&L.a[g][0][0]) + q * 4 * 1024;
+  const uint32_t la0 = lds_offset(&L.a[g][0][0]) + q * TM * 1024;
   const uint32_t lb0 = lds_offset(&L.b[0][0]) + (g * 16 + q * 4) * 1024;
   // K-major pieces of this lane: k-row 4 (4 q + i) + lane / 16 of the group's half, the
   // 8 columns of its physical slot lane & 15; byte offsets at k-tile 0
@@ -174,7 +186,7 @@ __device__ __forceinline__ void gemm_tile_mainloop(const TileOps& o, int nk, con
     } else {
       const char* ga = o.a + static_cast<size_t>(tt) * 128;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) dma16(la0 + static_cast<uint32_t>((t & 1) * 16384 + i * 1024), ga, o.aoff[i]);
+      for (int i = 0; i < TM; ++i) dma16(la0 + static_cast<uint32_t>((t & 1) * 16384 + i * 1024), ga, o.aoff[i]);
     }
   };
   auto dma_b = [&](int t) {
@@ -192,7 +204,7 @@ __device__ __forceinline__ void gemm_tile_mainloop(const TileOps& o, int nk, con
     }
   };
   const int sw = lds_swizzle(lane & 31);
-  u32x4 af[2][kTileTM], bf[2][kTileTN];
+  u32x4 af[2][TM], bf[2][kTileTN];
   auto read_half = [&](int t, int h) {   // operands of k steps 2h, 2h + 1 of pipeline tile t
     const u32x4* pa = &L.a[g][t & 1][0];
     const u32x4* pb = &L.b[t % 3][0];
@@ -200,7 +212,7 @@ __device__ __forceinline__ void gemm_tile_mainloop(const TileOps& o, int nk, con
     for (int kk = 0; kk < 2; ++kk) {
       const int ch = (4 * h + 2 * kk + (lane >> 5)) ^ sw;
 #pragma unroll
-      for (int i = 0; i < kTileTM; ++i)
+      for (int i = 0; i < TM; ++i)
         af[kk][i] = AKM ? read_km_operand(pa, i * 32, 2 * h + kk) : pa[(i * 32 + (lane & 31)) * 8 + ch];
 #pragma unroll
       for (int j = 0; j < kTileTN; ++j) {
@@ -214,7 +226,7 @@ __device__ __forceinline__ void gemm_tile_mainloop(const TileOps& o, int nk, con
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-      for (int i = 0; i < kTileTM; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < kTileTN; ++j) acc[i][j] = mfma_32x32x16(af[kk][i], bf[kk][j], acc[i][j]);
     __builtin_amdgcn_s_setprio(0);
@@ -223,7 +235,7 @@ __device__ __forceinline__ void gemm_tile_mainloop(const TileOps& o, int nk, con
   // prologue: this wave's A piece of tile 0 and B pieces of tiles 0 and 1
   if (EXTRA) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) dma16(la0 + static_cast<uint32_t>(i * 1024), x->a, x->aoff[i]);
+    for (int i = 0; i < TM; ++i) dma16(la0 + static_cast<uint32_t>(i * 1024), x->a, x->aoff[i]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) dma16(lb0 + static_cast<uint32_t>(i * 1024), x->b, x->boff[i]);
   } else {
@@ -245,7 +257,7 @@ __device__ __forceinline__ void gemm_tile_mainloop(const TileOps& o, int nk, con
     __builtin_amdgcn_sched_barrier(0);
     compute();
     __builtin_amdgcn_sched_barrier(0);
-    wait_vmcnt<4>();
+    wait_vmcnt<TM>();   // all but the A loads just issued
     tile_barrier();
     __builtin_amdgcn_sched_barrier(0);
     dma_b(m + 2);

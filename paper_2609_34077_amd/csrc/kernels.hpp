@@ -147,9 +147,9 @@ hipError_t launch_experts_bf16_decode(const ExpertArgs& a, const PermBuffers& pb
 // bf16, a serving-sized batch (batch.hip): few enough rows per expert that the weight stream bounds the
 // layer (with adapters for any number of tokens, else above kDecodeMaxT). batch_tile_rows: the row-tile size to permute
 // and launch with, 0 when the many-token path is faster; pool: experts the routing can select,
-// skew: 1, or with a soft prior the smaller share of them that it concentrates on.
+// peak: 1, or with a soft prior its largest entry over a uniform one's.
 // O: bf16 expert outputs [rows, d]; part: kTailPartBytes for the down projection's slices.
-int batch_tile_rows(int T, int K, int pool, float skew);
+int batch_tile_rows(int T, int K, int pool, float peak);
 hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int bm, int pool, uint16_t* H, uint16_t* O,
                                 float* part, void* y, hipStream_t stream, hipEvent_t* marks,
                                 const LoraArgs* lora = nullptr);

@@ -26,11 +26,14 @@ CASES = [
     _cfg(64, 8, 2, 1, 192, 320),                                      # 64-row tiles: one tile exactly
     _cfg(65, 8, 2, 1, 256, 192),                                      # ... and one row more
     _cfg(120, 8, 2, 0, 128, 2048, L.ROUTE_SOFT_PRIOR, KEEP4),         # 64-row tiles, split reduction
-    _cfg(121, 8, 2, 0, 128, 192, L.ROUTE_SOFT_PRIOR, KEEP4),          # 128-row tiles from here
+    _cfg(121, 8, 2, 0, 128, 192, L.ROUTE_SOFT_PRIOR, KEEP4),
+    _cfg(144, 8, 2, 0, 128, 192, L.ROUTE_SOFT_PRIOR, KEEP4),          # the last batch of 64-row tiles
+    _cfg(145, 8, 2, 0, 128, 192, L.ROUTE_SOFT_PRIOR, KEEP4),          # 128-row tiles from here
     _cfg(128, 8, 2, 1, 320, 128),                                     # one tile exactly
     _cfg(129, 8, 2, 1, 128, 2048),                                    # one row more, split reduction
     _cfg(208, 8, 2, 0, 256, 256, L.ROUTE_HARD_MASK, KEEP4),           # the last batch, four experts
     _cfg(209, 8, 2, 0, 256, 256, L.ROUTE_HARD_MASK, KEEP4),           # the many-token path
+    _cfg(906, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),   # the last, many experts
     _cfg(597, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),
     _cfg(40, 256, 16, 8, 192, 64),                                    # the most experts and shared experts
 ]
@@ -52,3 +55,16 @@ def test_batch_packed(cfg):
                                                (300, 64, 6, 2, 256, 192, 8)])
 def test_batch_lora(T, E, K, ns, d, F, rank):
     check_lora(_cfg(T, E, K, ns, d, F), rank=rank)
+
+
+# the many-token path's last tile of a group: 64, 128, 192 or 256 rows multiplied. Two experts take
+# every token, as the shared expert does, so a group holds T rows.
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("T", [129, 192, 193, 256, 257, 320, 321, 449])
+def test_tail_rows(T, packed):
+    check_layer(_cfg(T, 8, 2, 1, 256, 192, L.ROUTE_HARD_MASK, (0, 5)), packed=packed)
+
+
+@pytest.mark.parametrize("T", [192, 257, 321])
+def test_tail_rows_lora(T):
+    check_lora(_cfg(T, 8, 2, 1, 192, 320, L.ROUTE_HARD_MASK, (0, 5)), rank=8)
