@@ -202,7 +202,9 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void batch_gemm_kernel(
   // Neighbouring column tiles start at different chunks, so that the workgroups launched together do
   // not all read the same columns of the token and weight rows at once (1 to 3% of a layer:
   // Mixtral-shaped, 400 tokens, plain, 584 -> 573 us; DeepSeek-shaped, 700, row-major, 311 -> 304).
-  const int rot = nt * 13 % nc;
+  // Reductions of fewer than 16 chunks keep their order, which is the training forward's: such a
+  // layer's two forwards then agree bit for bit, and it is over before the start matters.
+  const int rot = nc < 16 ? 0 : nt * 13 % nc;
   // the adapters' chunk, in the first slice: weight rows of lora_b, token rows of U
   const bool extra = LORA && z == 0;
   uint32_t xoff[kPieces<BM>];
