@@ -149,3 +149,25 @@ def test_layer_backward_full_size_sampled():
         gx, _, _ = TR.expert_backward(xf[toks[sel_t]], dout, w(inp["w_gate_up"][e]), w(inp["w_down"][e]))
         np.add.at(ref_dx, sel_t, gx)
     _close(out["d_x"][torch.from_numpy(toks).cuda()], ref_dx, "d_x (sampled tokens)")
+
+
+# Unchosen experts' gradients are zeroed by the weight gradients themselves when they are no more than
+# the chosen ones (4 of 8 here, and over several 64-group words), by a fill otherwise (3 of 8, 12 of
+# 64); the last float4s of a matrix that the workgroups do not share evenly (d F / 4 odd multiples).
+@pytest.mark.parametrize("E,K,ns,keep,d,F", [(8, 2, 0, (0, 2, 5, 7), 320, 192), (8, 2, 0, (0, 2, 5), 320, 192),
+                                             (64, 6, 2, tuple(range(3, 63, 5)), 128, 192),
+                                             (130, 6, 1, tuple(range(0, 130, 2)) + tuple(range(1, 71, 2)), 64, 64)])
+def test_unchosen_experts_get_zeros(E, K, ns, keep, d, F):
+    cfg = synth.LayerConfig(f"bwd_zeros_e{E}_{len(keep)}", T=96, d=d, F=F, E=E, K=K, n_shared=ns,
+                            route_mode=L.ROUTE_HARD_MASK, gate_mode=L.GATE_P if ns else L.GATE_RENORM, mask_set=keep,
+                            seed=46)
+    U.say(cfg.name)
+    stale = [torch.full((n, a, b), float("nan"), device="cuda") for n in (E, ns) if n for a, b in ((2 * F, d), (d, F))]
+    del stale   # the gradients are allocated from this memory
+    inp, xf, idx_o, gate_o, dyf, out = _run(cfg, dy_seed=1)
+    chosen = np.zeros(E, bool)
+    chosen[np.unique(idx_o)] = True
+    for k in ("d_w_gate_up", "d_w_down"):
+        per = out[k].flatten(1).abs().amax(1).cpu().numpy()
+        assert np.isfinite(per).all(), k
+        assert ((per > 0) == chosen).all(), k
