@@ -74,15 +74,24 @@ __device__ __forceinline__ void lora_down(const uint16_t* __restrict__ src, cons
   const int kSub = tile_rows / kLoraRows;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int mt = block / kSub, sub = block % kSub;
-  if (mt >= tile_off[G]) return;
-  int lo = 0, hi = G;   // tile_off[lo] <= mt < tile_off[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (tile_off[mid] <= mt) lo = mid; else hi = mid;
+  // The group with tile_off[g] <= mt < tile_off[g + 1], one group per lane: a workgroup is short, and
+  // each step of a binary search is a round trip to memory (DeepSeek-shaped, 2000 tokens, gate/up:
+  // 40.8 -> 35.4 us at the least).
+  int g = -1, mt0 = 0, row0 = 0, row_end = 0;
+  for (int base = 0; base < G && g < 0; base += 64) {
+    const int q = min(base + lane, G - 1);
+    const int m0 = tile_off[q], m1 = tile_off[q + 1], r0 = offsets[q], r1 = offsets[q + 1];
+    const uint64_t hit = __ballot(m0 <= mt && mt < m1);
+    if (hit) {
+      const int l = __builtin_ctzll(hit);
+      g = min(base + l, G - 1);
+      mt0 = __builtin_amdgcn_readlane(m0, l);
+      row0 = __builtin_amdgcn_readlane(r0, l);
+      row_end = __builtin_amdgcn_readlane(r1, l);
+    }
   }
-  const int g = lo;
-  const int row0 = offsets[g] + (mt - tile_off[g]) * tile_rows + sub * kLoraRows;
-  const int row_end = offsets[g + 1];
+  if (g < 0) return;   // past the last tile
+  row0 += (mt - mt0) * tile_rows + sub * kLoraRows;
   if (row0 >= row_end) return;   // the whole workgroup leaves together
   const int rr = min(row0 + (lane & 15), row_end - 1);
   const uint16_t* xrow = src + static_cast<size_t>(row_tok ? row_tok[rr] : rr) * K + (lane >> 4) * 8;
@@ -95,27 +104,22 @@ __device__ __forceinline__ void lora_down(const uint16_t* __restrict__ src, cons
   f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
   const int steps = K / 32, per = (steps + kLoraWaves - 1) / kLoraWaves;
   const int s0 = min(wave * per, steps), s1 = min(s0 + per, steps);
-  int s = s0;
-  for (; s + kLoraUnroll <= s1; s += kLoraUnroll) {   // all loads of kLoraUnroll k-steps first
+  for (int s = s0; s < s1; s += kLoraUnroll) {   // all loads of kLoraUnroll k-steps first; zeros past s1
     u32x4 av[kLoraUnroll], bv0[kLoraUnroll], bv1[kLoraUnroll];
 #pragma unroll
     for (int u = 0; u < kLoraUnroll; ++u) {
+      const bool in = s + u < s1;
       const int k = (s + u) * 32;
-      av[u] = *reinterpret_cast<const u32x4*>(xrow + k);
-      bv0[u] = has0 ? *reinterpret_cast<const u32x4*>(b0 + k) : zero;
-      bv1[u] = has1 ? *reinterpret_cast<const u32x4*>(b1 + k) : zero;
+      av[u] = in ? *reinterpret_cast<const u32x4*>(xrow + k) : zero;
+      bv0[u] = in && has0 ? *reinterpret_cast<const u32x4*>(b0 + k) : zero;
+      bv1[u] = in && has1 ? *reinterpret_cast<const u32x4*>(b1 + k) : zero;
     }
 #pragma unroll
-    for (int u = 0; u < kLoraUnroll; ++u) {
-      acc0 = mfma_16x16x32(av[u], bv0[u], acc0);
-      if (two) acc1 = mfma_16x16x32(av[u], bv1[u], acc1);
-    }
-  }
-  for (; s < s1; ++s) {
-    const int k = s * 32;
-    const u32x4 av = *reinterpret_cast<const u32x4*>(xrow + k);
-    acc0 = mfma_16x16x32(av, has0 ? *reinterpret_cast<const u32x4*>(b0 + k) : zero, acc0);
-    if (two) acc1 = mfma_16x16x32(av, has1 ? *reinterpret_cast<const u32x4*>(b1 + k) : zero, acc1);
+    for (int u = 0; u < kLoraUnroll; ++u)
+      if (s + u < s1) {
+        acc0 = mfma_16x16x32(av[u], bv0[u], acc0);
+        if (two) acc1 = mfma_16x16x32(av[u], bv1[u], acc1);
+      }
   }
   // acc[i] is row 4 (lane >> 4) + i, column lane & 15 (second tile: + 16)
 #pragma unroll
