@@ -155,7 +155,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, const f32x16 (&
 // A group's last row tile multiplies (and loads) only its 64-row pieces that hold rows, the two wave
 // groups sharing them evenly: 256-row tiles of a DeepSeek-shaped batch of 2000 tokens are a third
 // padding. Layers at 2000 tokens: DeepSeek-shaped, soft prior 488 -> 401 us (with adapters
-// 556 -> 476), 1000 tokens 386 -> 317; Mixtral-shaped, 400 tokens 664 -> 592.
+// 555 -> 489), 1000 tokens 386 -> 317; Mixtral-shaped, 400 tokens 664 -> 592.
 // PACKED: the expert matrices are in the packed layout (kPackRows x kPackCols blocks).
 template <int EPI, bool LORA = false, bool PACKED = false>
 __global__ __launch_bounds__(GEMM_THREADS) void grouped_gemm_bf16(const GemmArgs p) {
