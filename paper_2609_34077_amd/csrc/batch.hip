@@ -32,9 +32,9 @@ namespace {
 
 constexpr int kW = 128;           // weight rows per workgroup (one packed group)
 constexpr int kCK = kPackCols;    // reduction values per chunk
-// Byte offset of a token row that is not there: past any operand, so that the load returns zeros
-// without touching memory.
-constexpr uint32_t kNoRow = 0xf0000000u;
+// Byte offset of a token row that is not there: past any operand (fewer than 2^31 elements of whole
+// 128-byte pieces, so at most 2^32 - 128 bytes); the load returns zeros without touching memory.
+constexpr uint32_t kNoRow = 0xfffffff0u;
 
 struct BatchArgs {
   const uint16_t* a;        // EPI 0: x [T, d] (rows via row_tok); EPI 1: H [rows, F]
@@ -72,15 +72,18 @@ __device__ __forceinline__ void stream_tile(const void* w, uint32_t wbytes, uint
   const int dst = (tid >> 3) * 8 + ((tid & 7) ^ lds_swizzle(tid >> 3));   // piece i: + kThreads * i
   const int sw = lds_swizzle(lane & 31);
   u32x4 reg[2][PER];
-  // Past the last chunk the buffers are empty: the loads return zeros without touching memory,
-  // and every step has the same loads behind the ones its stores wait for.
+  // Past the last chunk the buffers are empty and the scalar offset is 0 (the range check compares with
+  // the size less that offset, which must not wrap): the loads return zeros without touching memory, and
+  // every step has the same loads behind the ones its stores wait for.
   constexpr int kNt = 2;   // the load's non-temporal bit
   const int x = LORA && extra ? 1 : 0, steps = nc + x;
   auto load = [&](int ci, u32x4 (&r)[PER]) {
     const int c = LORA ? ci - x : ci;
-    const __amdgpu_buffer_rsrc_t wr = make_rsrc(w, c < nc ? wbytes : 0), ar = make_rsrc(a, c < nc ? abytes : 0);
+    const bool in = c < nc;
+    const __amdgpu_buffer_rsrc_t wr = make_rsrc(w, in ? wbytes : 0), ar = make_rsrc(a, in ? abytes : 0);
     const int rc = c + rot >= nc ? c + rot - nc : c + rot;   // walks the chunks from `rot` around
-    const uint32_t ws = w0 + static_cast<uint32_t>(rc) * wstep, as = a0 + static_cast<uint32_t>(rc) * (2 * kCK);
+    const uint32_t ws = in ? w0 + static_cast<uint32_t>(rc) * wstep : 0;
+    const uint32_t as = in ? a0 + static_cast<uint32_t>(rc) * (2 * kCK) : 0;
 #pragma unroll
     for (int i = 0; i < PER; ++i)
       r[i] = i < kPW ? __builtin_amdgcn_raw_buffer_load_b128(wr, off[i], ws, NT ? kNt : 0)
