@@ -315,6 +315,9 @@ static int layer_forward_impl(const maskmoe_layer_desc* desc, const void* x, con
     peak = static_cast<float>(top * d.E / sum);
   }
   const int batch_rows = bf16 && !train && !decode ? maskmoe::batch_tile_rows(d.T, d.K, pool, peak) : 0;
+  // the few-token path's partial sums are free here: at least 8 x 2 x 64 floats (F >= 64)
+  static_assert(maskmoe::kDecodeMaxSplitGateUp * 2 * 64 >= kMaxE + kMaxShared + 1, "P holds the wide tile offsets");
+  if (batch_rows) pb.wide_off = reinterpret_cast<int32_t*>(ws + w.P);
   if (decode) {  // one workgroup routes every token and then permutes them
     e = maskmoe::launch_route_permute(x, w_router, d.T, d.d, d.E, d.K, d.route_mode, d.gate_mode, mask, prior, idx,
                                       gate, router_logits, d.n_shared, maskmoe::kGemmBM, pb, stream);

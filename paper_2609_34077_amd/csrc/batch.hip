@@ -17,8 +17,9 @@
 // 256 token rows (one workgroup per CU) lost 15-60%: its loads, LDS accesses and products no
 // longer overlap.
 // Adapted experts (LORA) take the adapters' term as one more chunk, as the many-token path does.
-// The down projection splits its reduction when the tiles alone would leave the chip idle; its
-// fp32 slices are added, in order, by the combine.
+// Every sum is formed in the many-token path's order, so that a layer gives the same bits on either
+// (and as its training forward): chunks in ascending order, and a down projection whose 256 x 256
+// tile that path would split (tile_slices) in the same slices, which batch_fixup_kernel adds in order.
 
 #include "common.hpp"
 #include "gemm_tile.hpp"
@@ -44,11 +45,13 @@ struct BatchArgs {
   const int32_t* offsets;   // [G+1]
   const int32_t* tile_off;  // [G+1], tiles of BM rows
   uint16_t* out;            // EPI 0: H [rows, F]; EPI 1: O [rows, d]
-  float* part;              // EPI 1 with split > 1: [split, rows, d] fp32
+  const int32_t* wide_off;  // [G+1], tiles of kGemmBM rows
+  float* part;              // EPI 1: partial tiles, kTailSlots x [256 rows][256 columns] fp32
   int G, E, N, K, F, rows;  // N: output columns (F or d), K: reduction length
   const uint16_t* lora_u;   // LORA: rank projections of a's rows, bf16 [rows, 64]
   const uint16_t* lora_b;   // LORA: the scaled adapter rows beside the weight rows, bf16 [G, weight rows, 64]
-  int n_tiles, split, a_rows;   // a_rows: rows of a (T or rows)
+  int n_tiles, split, a_rows;   // split: workgroups that share a tile's slices; a_rows: rows of a (T or rows)
+  int cu_xcd;
 };
 
 constexpr int kThreads = 256, kRowsPerPiece = kThreads / 8;
@@ -58,11 +61,11 @@ constexpr int kPieces = kPW + BM / kRowsPerPiece;
 
 // The stream of one tile: acc += W X^T over nc chunks. off[]: this thread's 16-byte pieces of a
 // chunk (the first PW are weights, in w from byte w0 + chunk * wstep; then tokens, in a from a0 + 128 chunk).
-// rot: the chunk to start with. NT: non-temporal weight loads. LORA: with `extra`, one more chunk goes
+// NT: non-temporal weight loads. LORA: with `extra`, one more chunk goes
 // first, the adapters' term [s B] U^T (weight pieces in xw at xoff[], token pieces in xu).
 template <int BM, bool NT, bool LORA>
 __device__ __forceinline__ void stream_tile(const void* w, uint32_t wbytes, uint32_t w0, uint32_t wstep,
-                                            const void* a, uint32_t abytes, uint32_t a0, int nc, int rot,
+                                            const void* a, uint32_t abytes, uint32_t a0, int nc,
                                             const uint32_t (&off)[kPieces<BM>], u32x4 (*lds)[(kW + BM) * 8], int wrow0,
                                             int wrow1, int trow, f32x16 (&acc)[2][BM / 64], bool extra,
                                             const void* xw, uint32_t xwbytes, const void* xu, uint32_t xubytes,
@@ -81,9 +84,8 @@ __device__ __forceinline__ void stream_tile(const void* w, uint32_t wbytes, uint
     const int c = LORA ? ci - x : ci;
     const bool in = c < nc;
     const __amdgpu_buffer_rsrc_t wr = make_rsrc(w, in ? wbytes : 0), ar = make_rsrc(a, in ? abytes : 0);
-    const int rc = c + rot >= nc ? c + rot - nc : c + rot;   // walks the chunks from `rot` around
-    const uint32_t ws = in ? w0 + static_cast<uint32_t>(rc) * wstep : 0;
-    const uint32_t as = in ? a0 + static_cast<uint32_t>(rc) * (2 * kCK) : 0;
+    const uint32_t ws = in ? w0 + static_cast<uint32_t>(c) * wstep : 0;
+    const uint32_t as = in ? a0 + static_cast<uint32_t>(c) * (2 * kCK) : 0;
 #pragma unroll
     for (int i = 0; i < PER; ++i)
       r[i] = i < kPW ? __builtin_amdgcn_raw_buffer_load_b128(wr, off[i], ws, NT ? kNt : 0)
@@ -154,20 +156,21 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void batch_gemm_kernel(
   const int mtiles = p.tile_off[g + 1] - p.tile_off[g];
   const int within = lid - p.tile_off[g] * per;
   const int m = within % mtiles, nz = within / mtiles;
-  const int nt = nz / p.split, z = nz % p.split;
+  const int nt = nz / p.split;
   const int row0 = p.offsets[g] + m * BM, row_end = p.offsets[g + 1];
-  const int nc = p.K / kCK / p.split;          // chunks of this slice
-  const int c0 = z * nc;
+  TileSlices sl{1, -1};
+  if (EPI == 1 && tail_can_split(1, p.K / kCK)) {
+    const int wide_live = p.wide_off[p.G], wide_tiles = (p.N + kTileN - 1) / kTileN;
+    sl = tile_slices(grouped_tile_lid(p.wide_off[g] + m * BM / kTileM, nt * kW / kTileN, wide_live, wide_tiles),
+                     wide_live * wide_tiles, p.cu_xcd, p.K / kCK, true);
+  }
+  const int nc = p.K / kCK / sl.s;             // chunks of a slice
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;     // token part, weight half
   const int n0 = nt * (EPI == 0 ? kW / 2 : kW);
   const size_t mat = static_cast<size_t>(EPI == 0 ? 2 * p.F : p.N) * p.K;
   const uint16_t* wg = g < p.E ? p.w + g * mat : p.ws + (g - p.E) * mat;
-  // byte offsets of chunk c0 within the expert's matrix (below 2^32: 2 F d < 2^31 elements)
-  const uint32_t w0 = PACKED ? 2u * (static_cast<uint32_t>(nt) * kW * p.K + static_cast<uint32_t>(c0) * kPackBlock)
-                             : 2u * static_cast<uint32_t>(c0) * kCK;
-  const uint32_t a0 = 2u * static_cast<uint32_t>(c0) * kCK;
   const uint32_t wbytes = static_cast<uint32_t>(2 * mat), abytes = 2u * static_cast<uint32_t>(p.a_rows) * p.K;
 
   // Piece i of this thread: row 32 i + tid / 8 of the stage (weight rows, then token rows), 16
@@ -189,27 +192,13 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void batch_gemm_kernel(
       off[i] = r < row_end ? static_cast<uint32_t>((EPI == 0 ? p.row_tok[r] : r) * p.K + pc * 8) * 2u : kNoRow;
     }
   }
-  f32x16 acc[2][TN];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
   // fragment rows of the stage: weights (EPI 0: gate rows and the matching up rows), tokens
   const int l32 = lane & 31;
   const int wrow0 = (EPI == 0 ? wn * 32 : wn * 64) + l32, wrow1 = wrow0 + (EPI == 0 ? kW / 2 : 32);
   const int trow = kW + wm * 32 * TN + l32;
   constexpr int wstep = 2 * (PACKED ? kPackBlock : kCK);
-  // Neighbouring column tiles start at different chunks, so that the workgroups launched together do
-  // not all read the same columns of the token and weight rows at once (1 to 3% of a layer:
-  // Mixtral-shaped, 400 tokens, plain, 584 -> 573 us; DeepSeek-shaped, 700, row-major, 311 -> 304).
-  // Reductions of fewer than 16 chunks keep their order, which is the training forward's: such a
-  // layer's two forwards then agree bit for bit, and it is over before the start matters.
-  const int rot = nc < 16 ? 0 : nt * 13 % nc;
   // the adapters' chunk, in the first slice: weight rows of lora_b, token rows of U
-  const bool extra = LORA && z == 0;
   uint32_t xoff[kPieces<BM>];
   const void* xw = nullptr;
   const uint32_t wrows = EPI == 0 ? 2 * p.F : p.N;
@@ -227,50 +216,108 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void batch_gemm_kernel(
       }
     }
   }
-  if (mtiles == 1)
-    stream_tile<BM, true, LORA>(wg, wbytes, w0, wstep, p.a, abytes, a0, nc, rot, off, lds, wrow0, wrow1, trow, acc, extra, xw, wrows * 128u, p.lora_u,
-                                static_cast<uint32_t>(p.rows) * 128u, xoff);
-  else
-    stream_tile<BM, false, LORA>(wg, wbytes, w0, wstep, p.a, abytes, a0, nc, rot, off, lds, wrow0, wrow1, trow, acc, extra, xw, wrows * 128u, p.lora_u,
-                                static_cast<uint32_t>(p.rows) * 128u, xoff);
 
-  // acc[i][j][4 q + e]: weight row 8 q + 4 (lane >> 5) + e of fragment i, token row lane & 31 of
-  // fragment j
+  for (int z = nz % p.split; z < sl.s; z += p.split) {   // this workgroup's slices (EPI 0: one)
+    const int c0 = z * nc;
+    // byte offsets of chunk c0 within the expert's matrix (below 2^32: 2 F d < 2^31 elements)
+    const uint32_t w0 = PACKED ? 2u * (static_cast<uint32_t>(nt) * kW * p.K + static_cast<uint32_t>(c0) * kPackBlock)
+                               : 2u * static_cast<uint32_t>(c0) * kCK;
+    const uint32_t a0 = 2u * static_cast<uint32_t>(c0) * kCK;
+    const bool extra = LORA && z == 0;
+    f32x16 acc[2][TN];
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int row = row0 + wm * 32 * TN + 32 * j + l32;
-    if (row >= row_end) continue;
-    if (EPI == 0) {
-      uint16_t* dsth = p.out + static_cast<size_t>(row) * p.F + n0 + wn * 32 + 4 * (lane >> 5);
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float h[4];
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) h[e] = silu(acc[0][j][4 * q + e]) * acc[1][j][4 * q + e];
-        uint2 v;
-        v.x = f32x2_to_bf16x2(h[0], h[1]);
-        v.y = f32x2_to_bf16x2(h[2], h[3]);
-        *reinterpret_cast<uint2*>(dsth + 8 * q) = v;
-      }
-    } else {
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    if (mtiles == 1)
+      stream_tile<BM, true, LORA>(wg, wbytes, w0, wstep, p.a, abytes, a0, nc, off, lds, wrow0, wrow1, trow, acc, extra, xw,
+                                  wrows * 128u, p.lora_u, static_cast<uint32_t>(p.rows) * 128u, xoff);
+    else
+      stream_tile<BM, false, LORA>(wg, wbytes, w0, wstep, p.a, abytes, a0, nc, off, lds, wrow0, wrow1, trow, acc, extra, xw,
+                                   wrows * 128u, p.lora_u, static_cast<uint32_t>(p.rows) * 128u, xoff);
+
+    // acc[i][j][4 q + e]: weight row 8 q + 4 (lane >> 5) + e of fragment i, token row lane & 31 of
+    // fragment j
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < TN; ++j) {
+      const int row = row0 + wm * 32 * TN + 32 * j + l32;
+      if (row >= row_end) continue;
+      if (EPI == 0) {
+        uint16_t* dsth = p.out + static_cast<size_t>(row) * p.F + n0 + wn * 32 + 4 * (lane >> 5);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int col = n0 + wn * 64 + 32 * i + 8 * q + 4 * (lane >> 5);
-          if (col >= p.N) continue;   // N % 64 == 0: four columns are all inside or all outside
-          const f32x16& a = acc[i][j];
-          if (p.split > 1) {
-            *reinterpret_cast<float4*>(p.part + (static_cast<size_t>(z) * p.rows + row) * p.N + col) =
-                make_float4(a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]);
-          } else {
-            uint2 v;
-            v.x = f32x2_to_bf16x2(a[4 * q], a[4 * q + 1]);
-            v.y = f32x2_to_bf16x2(a[4 * q + 2], a[4 * q + 3]);
-            *reinterpret_cast<uint2*>(p.out + static_cast<size_t>(row) * p.N + col) = v;
-          }
+          float h[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) h[e] = silu(acc[0][j][4 * q + e]) * acc[1][j][4 * q + e];
+          uint2 v;
+          v.x = f32x2_to_bf16x2(h[0], h[1]);
+          v.y = f32x2_to_bf16x2(h[2], h[3]);
+          *reinterpret_cast<uint2*>(dsth + 8 * q) = v;
         }
+      } else {
+        float* slot = sl.s > 1 ? p.part + static_cast<size_t>(sl.slot + z) * kTailTileFloats : nullptr;
+        const int wrow = m * BM % kTileM + row - row0, wcol = n0 % kTileN;           // within the 256 x 256 tile
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int c = wn * 64 + 32 * i + 8 * q + 4 * (lane >> 5);
+            if (n0 + c >= p.N) continue;   // N % 64 == 0: four columns are all inside or all outside
+            const f32x16& a = acc[i][j];
+            if (sl.s > 1) {
+              *reinterpret_cast<float4*>(slot + wrow * kTileN + wcol + c) =
+                  make_float4(a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]);
+            } else {
+              uint2 v;
+              v.x = f32x2_to_bf16x2(a[4 * q], a[4 * q + 1]);
+              v.y = f32x2_to_bf16x2(a[4 * q + 2], a[4 * q + 3]);
+              *reinterpret_cast<uint2*>(p.out + static_cast<size_t>(row) * p.N + n0 + c) = v;
+            }
+          }
+      }
     }
+  }
+}
+
+// Adds the slices of the down projection's split tiles in slice order and stores their rows of O:
+// kFixRows rows of one tile per workgroup, tail tile t of XCD xcd at workgroup 8 (t * parts + part) + xcd.
+constexpr int kFixRows = 16;
+__global__ __launch_bounds__(kThreads) void batch_fixup_kernel(const BatchArgs p, int parts) {
+  const int b = blockIdx.x, xcd = b & 7, t = (b >> 3) / parts, part = (b >> 3) % parts;
+  const int mt_live = p.wide_off[p.G], n_tiles = (p.N + kTileN - 1) / kTileN;
+  const XcdShare x = xcd_share(xcd, mt_live * n_tiles, p.cu_xcd, p.K / kCK, true);
+  if (x.s == 1 || t >= x.r) return;
+  int mt, nt;
+  grouped_tile_coords(x.base + x.full + t, mt_live, n_tiles, mt, nt);
+  int lo = 0, hi = p.G;                        // wide_off[lo] <= mt < wide_off[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (p.wide_off[mid] <= mt) lo = mid; else hi = mid;
+  }
+  const int row0 = p.offsets[lo] + (mt - p.wide_off[lo]) * kTileM, row_end = min(p.offsets[lo + 1], row0 + kTileM);
+  const int c = (threadIdx.x & 63) * 4, col = nt * kTileN + c;
+  if (col >= p.N) return;
+  const float* src = p.part + static_cast<size_t>(xcd * kTailSlotsPerXcd + t * x.s) * kTailTileFloats + c;
+#pragma unroll
+  for (int i = 0; i < kFixRows / 4; ++i) {
+    const int r = part * kFixRows + 4 * i + (threadIdx.x >> 6);
+    if (row0 + r >= row_end) break;
+    float4 v[kTailMaxSplit];
+#pragma unroll
+    for (int z = 0; z < kTailMaxSplit; ++z)
+      if (z < x.s) v[z] = *reinterpret_cast<const float4*>(src + static_cast<size_t>(z) * kTailTileFloats + r * kTileN);
+    float4 a = v[0];
+#pragma unroll
+    for (int z = 1; z < kTailMaxSplit; ++z)
+      if (z < x.s) {
+        a.x += v[z].x; a.y += v[z].y; a.z += v[z].z; a.w += v[z].w;
+      }
+    uint2 o;
+    o.x = f32x2_to_bf16x2(a.x, a.y);
+    o.y = f32x2_to_bf16x2(a.z, a.w);
+    *reinterpret_cast<uint2*>(p.out + static_cast<size_t>(row0 + r) * p.N + col) = o;
   }
 }
 
@@ -313,19 +360,6 @@ int batch_tile_rows(int T, int K, int pool, float peak) {
   return (pool >= 32 ? avg <= 85 : avg * peak <= 104) ? 128 : 0;
 }
 
-// Slices of the down projection's reduction: up to about 600 workgroups, 16 chunks a slice.
-// (Mixtral-shaped: 256 workgroups in one slice leave a third of the resident slots empty; two
-// slices 480 us a layer at 96 tokens, four 490; at 300 tokens one slice 637, two 624, four 631.)
-constexpr int kDownTarget = 600;
-static int batch_split(int tiles, int rows, int d, int F) {
-  const int chunks = F / kCK;
-  int s = 1;
-  while (s < 8 && tiles * s * 2 <= kDownTarget && chunks % (2 * s) == 0 && chunks / (2 * s) >= 16 &&
-         static_cast<int64_t>(rows) * d * 4 * 2 * s <= static_cast<int64_t>(kTailPartBytes))
-    s *= 2;
-  return s;
-}
-
 hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int bm, int pool, uint16_t* H, uint16_t* O,
                                 float* part, void* y, hipStream_t stream, hipEvent_t* marks, const LoraArgs* lora) {
   const int64_t TK = static_cast<int64_t>(a.T) * a.K;
@@ -336,6 +370,9 @@ hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int 
   p.row_tok = pb.row_tok;
   p.offsets = pb.offsets;
   p.tile_off = pb.tile_off;
+  p.wide_off = pb.wide_off;
+  p.part = part;
+  p.cu_xcd = device_cus_per_xcd();
   p.G = a.E + a.n_shared; p.E = a.E; p.F = a.F;
   p.rows = a.T * (a.K + a.n_shared);
 
@@ -367,17 +404,29 @@ hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int 
   p.w = static_cast<const uint16_t*>(a.w_down);
   p.ws = static_cast<const uint16_t*>(a.ws_down);
   p.out = O;
-  p.part = part;
   p.N = a.d; p.K = a.F; p.a_rows = p.rows;
   p.n_tiles = (a.d + kW - 1) / kW;
-  const int active = static_cast<int>(std::min<int64_t>(pool, TK));
-  const int tiles = static_cast<int>(std::max<int64_t>(active, TK / bm)) + shared_tiles;   // about this many row tiles
-  p.split = batch_split(tiles * p.n_tiles, p.rows, a.d, a.F);
+  // One workgroup per slice of the likely number of tiles (fewer experts chosen, in more slices: a
+  // workgroup takes several in turn).
+  const bool sliced = tail_can_split(1, a.F / kCK);
+  const int wide_tiles = (a.d + kTileN - 1) / kTileN;
+  if (sliced) {
+    const int active = static_cast<int>(std::min<int64_t>(pool, TK));
+    const int mt = static_cast<int>(std::max<int64_t>(active, TK / kTileM)) + a.n_shared * ((a.T + kTileM - 1) / kTileM);
+    p.split = xcd_share(0, mt * wide_tiles, p.cu_xcd, a.F / kCK, true).s;
+  }
   err = launch<1>(bm, a.packed, max_tiles * p.n_tiles * p.split, p, stream);
   if (err != hipSuccess) return err;
+  if (sliced) {
+    const int64_t mt = TK / kTileM + nonempty + a.n_shared * ((a.T + kTileM - 1) / kTileM);   // the most tiles
+    const int tails = static_cast<int>(std::min<int64_t>((mt * wide_tiles + 7) / 8, kTailSlotsPerXcd));
+    const int parts = (std::min(a.T, kTileM) + kFixRows - 1) / kFixRows;   // a group holds at most T rows
+    hipLaunchKernelGGL(batch_fixup_kernel, dim3(8 * tails * parts), dim3(kThreads), 0, stream, p, parts);
+    err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
   record_mark(marks, 1, stream);
-  err = p.split > 1 ? launch_combine(a, pb, part, false, p.split, y, stream)
-                    : launch_combine(a, pb, O, true, 1, y, stream);
+  err = launch_combine(a, pb, O, true, 1, y, stream);
   record_mark(marks, 2, stream);
   return err;
 }

@@ -57,12 +57,6 @@ struct GemmArgs {
   int cu_xcd;               // workgroups an XCD runs at once (one per CU)
 };
 
-// Only the down GEMM splits its tail tiles (tile_job in gemm_tile.hpp): its long reductions
-// amortise a slice's fixed costs, and the gate/up GEMM's epilogue needs whole sums. Measured,
-// slices shorter than 16 k-tiles and splits of the gate/up tiles (with SwiGLU applied in the
-// fix-up) gained nothing over the partial round they save.
-__host__ __device__ constexpr bool tail_can_split(int epi, int nk) { return epi == 1 && tail_splittable(nk); }
-
 __device__ __forceinline__ int find_group(const int32_t* tile_off, int G, int mt) {
   int lo = 0, hi = G;  // tile_off[lo] <= mt < tile_off[hi]
   while (hi - lo > 1) {

@@ -298,6 +298,13 @@ __device__ __forceinline__ void grouped_tile_coords(int lid, int mt_max, int n_t
   mt = within / gsize;
 }
 
+// The inverse: the logical tile of (mt, nt).
+__device__ __forceinline__ int grouped_tile_lid(int mt, int nt, int mt_max, int n_tiles) {
+  constexpr int GN = 4;
+  const int first_n = nt / GN * GN;
+  return first_n * mt_max + mt * min(n_tiles - first_n, GN) + nt - first_n;
+}
+
 // Tail split. The hardware deals workgroups round-robin over the 8 XCDs; XCD x takes a
 // contiguous range of the live tiles (the partition of xcd_tile_id) and runs cu_xcd of them at
 // a time. All tiles cost the same, so the r tiles of an XCD's last, partial round would leave
@@ -312,6 +319,12 @@ constexpr int kTailMaxSplit = 8, kTailMinK = 16;
 // a split into two slices is possible: nk even, >= kTailMinK k-tiles each
 __host__ __device__ constexpr bool tail_splittable(int nk) { return nk % 2 == 0 && nk / 2 >= kTailMinK; }
 
+// Of the forward GEMMs (epi 0 gate/up, 1 down) only the down GEMM splits its tail tiles: its long
+// reductions amortise a slice's fixed costs, and the gate/up GEMM's epilogue needs whole sums.
+// Measured, slices shorter than 16 k-tiles and splits of the gate/up tiles (with SwiGLU applied in
+// the fix-up) gained nothing over the partial round they save.
+__host__ __device__ constexpr bool tail_can_split(int epi, int nk) { return epi == 1 && tail_splittable(nk); }
+
 struct TileJob {
   int lid;    // logical tile (grouped_tile_coords order)
   int z, s;   // reduction slice z of s (s == 1: the whole tile)
@@ -322,14 +335,14 @@ struct XcdShare {
   int base, full, r, s;   // first tile, tiles run whole, tail tiles, their slices
 };
 
-__device__ __forceinline__ XcdShare xcd_share(int xcd, int live, int cu_xcd, int nk, bool split_ok) {
+__host__ __device__ __forceinline__ XcdShare xcd_share(int xcd, int live, int cu_xcd, int nk, bool split_ok) {
   XcdShare x;
   const int q = live >> 3, rem = live & 7;
   const int count = q + (xcd < rem ? 1 : 0);
   x.base = xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q;
   x.full = count / cu_xcd * cu_xcd;
   x.r = count - x.full;
-  const int cap = min(cu_xcd, kTailSlotsPerXcd);
+  const int cap = cu_xcd < kTailSlotsPerXcd ? cu_xcd : kTailSlotsPerXcd;
   x.s = 1;
   if (split_ok && x.r > 0)
     for (int s = 2; s <= kTailMaxSplit; s *= 2)
@@ -356,6 +369,19 @@ __device__ __forceinline__ bool tile_job(int bid, int live, int cu_xcd, int nk, 
   j.s = x.s;
   j.slot = xcd * kTailSlotsPerXcd + t;
   return true;
+}
+
+// How logical tile lid is summed: in s slices, whose partial tiles take the slots from `slot` on.
+struct TileSlices {
+  int s, slot;
+};
+__device__ __forceinline__ TileSlices tile_slices(int lid, int live, int cu_xcd, int nk, bool split_ok) {
+  const int q = live >> 3, rem = live & 7, big = rem * (q + 1);
+  const int xcd = lid < big ? lid / (q + 1) : rem + (lid - big) / q;   // lid < live: q > 0 past `big`
+  const XcdShare x = xcd_share(xcd, live, cu_xcd, nk, split_ok);
+  const int t = lid - x.base - x.full;   // tail tile
+  if (t < 0 || x.s == 1) return {1, -1};
+  return {x.s, xcd * kTailSlotsPerXcd + t * x.s};
 }
 
 // Partial-tile slot layout: float4 e of thread tid at [e][tid] (coalesced for both sides).

@@ -8,9 +8,13 @@
 
 namespace maskmoe {
 
+// Row-tile size of the bf16 grouped GEMMs (the permutation counts tiles of this many rows).
+constexpr int kGemmBM = 256;
+
 // Group the T*K routed (token, slot) entries by expert, stably in entry order, and append
 // n_shared groups of all T tokens. Writes offsets/tile_off [G+1], active [G], n_active [1],
-// perm/inv [T*K], row_tok [T*(K+n_shared)], with G = E + n_shared.
+// perm/inv [T*K], row_tok [T*(K+n_shared)], with G = E + n_shared. wide_off, when given: as tile_off
+// in row tiles of kGemmBM (launch_permute only).
 struct PermBuffers {
   int32_t* offsets;
   int32_t* tile_off;
@@ -19,6 +23,7 @@ struct PermBuffers {
   int32_t* perm;
   int32_t* inv;
   int32_t* row_tok;
+  int32_t* wide_off = nullptr;
 };
 // Router logits + softmax + mask/prior Top-K + gates for layers [0, L) of w_router
 // ([L, E, d]); host `mask` [L, E] (HARD_MASK) or `prior` [L, E] (SOFT_PRIOR), unused for
@@ -54,8 +59,6 @@ inline int permute_chunks(int T, int K) {
 hipError_t launch_permute(const int32_t* idx, int T, int K, int E, int n_shared, int tile_rows,
                           const PermBuffers& pb, int32_t* chunk_counts, hipStream_t stream);
 
-// Row-tile size of the bf16 grouped GEMMs (the permutation counts tiles of this many rows).
-constexpr int kGemmBM = 256;
 // Tokens at or below which the bf16 layer uses the weight-streaming decode kernels.
 constexpr int kDecodeMaxT = 16;
 
@@ -148,7 +151,8 @@ hipError_t launch_experts_bf16_decode(const ExpertArgs& a, const PermBuffers& pb
 // layer (with adapters for any number of tokens, else above kDecodeMaxT). batch_tile_rows: the row-tile size to permute
 // and launch with, 0 when the many-token path is faster; pool: experts the routing can select,
 // peak: 1, or with a soft prior its largest entry over a uniform one's.
-// O: bf16 expert outputs [rows, d]; part: kTailPartBytes for the down projection's slices.
+// O: bf16 expert outputs [rows, d]; part: kTailPartBytes for the down projection's slices; pb.wide_off
+// is needed. Bit-identical to launch_experts_bf16.
 int batch_tile_rows(int T, int K, int pool, float peak);
 hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int bm, int pool, uint16_t* H, uint16_t* O,
                                 float* part, void* y, hipStream_t stream, hipEvent_t* marks,

@@ -80,6 +80,16 @@ __device__ __forceinline__ void permute_scan_groups(int* total, int T, int E, in
     toff += til[i];
   }
   if (lane == kWave - 1) pb.n_active[0] = na;
+  if (!pb.wide_off) return;
+  int sw = 0;
+#pragma unroll
+  for (int i = 0; i < kMaxPG; ++i) sw += (cnt[i] + kGemmBM - 1) / kGemmBM;
+  int woff = wave_inclusive_sum(sw) - sw;
+#pragma unroll
+  for (int i = 0; i < kMaxPG; ++i) {
+    if (i < PG && g0 + i <= G) pb.wide_off[g0 + i] = woff;
+    woff += (cnt[i] + kGemmBM - 1) / kGemmBM;
+  }
 }
 
 // Orders LDS accesses of the lanes of one wavefront (which execute them in order) for the compiler.

@@ -7,7 +7,7 @@
   error is bounded by 1e-4 (1e-5 for single dot products) times the sum of the absolute values
   of the terms it adds up.
 * maskmoe_layer_forward_train: the logits and per-slot expert outputs against the oracle, y
-  identical to maskmoe_layer_forward.
+  identical to maskmoe_layer_forward above 16 tokens, at small and at model widths.
 * the whole step end to end (GPU forward, then GPU backward) against the oracle's forward and
   backward, on a case without near-ties (identical routing sets).
 """
@@ -120,6 +120,55 @@ def _layer(cfg):
     inp = synth.make_layer(cfg)
     dd = {k: U.dev(inp[k]) for k in ("x", "w_router", "w_gate_up", "w_down")}
     return inp, dd
+
+
+# Above 16 tokens the two forwards give the same bits, whichever expert kernels each takes: the
+# inference forward of a serving batch streams the weights through 64- or 128-row tiles, the training
+# forward always through the many-token path's 256 x 256 tiles, whose last round on an XCD is summed in
+# slices. Both model shapes at serving sizes, and rounds of every kind: one short round in 8, 4 and 2
+# slices, XCDs with and without slices (132 tiles), a full round behind the split one (264 tiles), an odd
+# number of 64-column chunks, more tokens than a 256-row tile in the shared group, experts that the
+# routing leaves out (fewer tiles, more slices than expected).
+@pytest.mark.parametrize("T,d,F,E,K,ns,mode,kept", [
+    (96, 4096, 14336, 8, 2, 0, L.ROUTE_SOFT_PRIOR, (0, 2, 5, 7)),
+    (208, 4096, 14336, 8, 2, 0, L.ROUTE_HARD_MASK, (0, 2, 5, 7)),
+    (333, 2048, 1408, 64, 6, 2, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),
+    (96, 1088, 2048, 8, 2, 0, L.ROUTE_PLAIN, ()),
+    (130, 1024, 4096, 8, 2, 1, L.ROUTE_PLAIN, ()),
+    (40, 4096, 4096, 8, 2, 0, L.ROUTE_SOFT_PRIOR, (1, 4)),
+    (300, 1024, 2048, 33, 1, 0, L.ROUTE_PLAIN, ()),
+    (512, 1024, 2048, 66, 1, 0, L.ROUTE_PLAIN, ()),
+    (600, 320, 2112, 64, 2, 1, L.ROUTE_PLAIN, ()),
+    (600, 320, 4096, 40, 2, 1, L.ROUTE_PLAIN, ()),
+])
+def test_forward_train_same_bits(T, d, F, E, K, ns, mode, kept):
+    U.say(f"forward and training forward T={T} d={d} F={F} E={E} K={K} shared={ns} mode={mode}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + d)
+
+    def rand(shape, std):
+        return torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16).mul_(std)
+
+    mask = synth.binary_mask(E, kept) if mode == L.ROUTE_HARD_MASK else None
+    prior = synth.concentrated_prior(E, kept, 20.0 if len(kept) == 2 else 1.0) if mode == L.ROUTE_SOFT_PRIOR else None
+    gate_mode = L.GATE_P if ns else L.GATE_RENORM
+    x, wr = rand((T, d), 1.0), rand((E, d), 0.02)
+    gu, dn = rand((E, 2 * F, d), d ** -0.5), rand((E, d, F), F ** -0.5)
+    sh = dict(ws_gate_up=rand((ns, 2 * F, d), d ** -0.5), ws_down=rand((ns, d, F), F ** -0.5)) if ns else {}
+    kw = dict(mask=mask, prior=prior, **sh)
+    y_train, idx, gate, _, _ = L.maskmoe_layer_forward_train(x, wr, gu, dn, K, mode, gate_mode, **kw)
+    idx1, gate1 = torch.empty_like(idx), torch.empty_like(gate)
+    y = L.maskmoe_layer_forward(x, wr, gu, dn, K, mode, gate_mode, topk_idx=idx1, topk_gate=gate1, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(idx, idx1) and torch.equal(gate, gate1)
+    assert torch.equal(y, y_train)
+    if d % 128 == 0:
+        pgu, pdn = L.maskmoe_pack_expert_weights(gu, dn)
+        if ns:
+            kw["ws_gate_up"], kw["ws_down"] = L.maskmoe_pack_expert_weights(sh["ws_gate_up"], sh["ws_down"])
+        yp = L.maskmoe_layer_forward(x, wr, pgu, pdn, K, mode, gate_mode, weight_layout=L.LAYOUT_PACKED, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(yp, y_train)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
