@@ -52,6 +52,7 @@ struct BatchArgs {
   const uint16_t* lora_b;   // LORA: the scaled adapter rows beside the weight rows, bf16 [G, weight rows, 64]
   int n_tiles, split, a_rows;   // split: workgroups that share a tile's slices; a_rows: rows of a (T or rows)
   int cu_xcd;
+  int skew;                 // batch_skewed: the many-token path's tiles are taken instead
 };
 
 constexpr int kThreads = 256, kRowsPerPiece = kThreads / 8;
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void batch_gemm_kernel(
 
   const int per = p.n_tiles * p.split;         // jobs per row tile
   const int live = p.tile_off[p.G] * per;
-  if (static_cast<int>(blockIdx.x) >= live) return;
+  if (static_cast<int>(blockIdx.x) >= live || batch_skewed(p.tile_off[p.G], p.wide_off[p.G], p.skew)) return;
   const int lid = xcd_tile_id(live);
   int lo = 0, hi = p.G;                        // tile_off[lo] <= lid / per < tile_off[hi]
   const int mt = lid / per;
@@ -297,23 +298,43 @@ __global__ __launch_bounds__(kThreads) void batch_fixup_kernel(const BatchArgs p
     if (p.wide_off[mid] <= mt) lo = mid; else hi = mid;
   }
   const int row0 = p.offsets[lo] + (mt - p.wide_off[lo]) * kTileM, row_end = min(p.offsets[lo + 1], row0 + kTileM);
-  const int c = (threadIdx.x & 63) * 4, col = nt * kTileN + c;
-  if (col >= p.N) return;
-  const float* src = p.part + static_cast<size_t>(xcd * kTailSlotsPerXcd + t * x.s) * kTailTileFloats + c;
-#pragma unroll
-  for (int i = 0; i < kFixRows / 4; ++i) {
-    const int r = part * kFixRows + 4 * i + (threadIdx.x >> 6);
-    if (row0 + r >= row_end) break;
+  const float* src = p.part + static_cast<size_t>(xcd * kTailSlotsPerXcd + t * x.s) * kTailTileFloats;
+  auto sum = [&](int off) {   // four values at float offset off of every slice
     float4 v[kTailMaxSplit];
 #pragma unroll
     for (int z = 0; z < kTailMaxSplit; ++z)
-      if (z < x.s) v[z] = *reinterpret_cast<const float4*>(src + static_cast<size_t>(z) * kTailTileFloats + r * kTileN);
+      if (z < x.s) v[z] = *reinterpret_cast<const float4*>(src + static_cast<size_t>(z) * kTailTileFloats + off);
     float4 a = v[0];
 #pragma unroll
     for (int z = 1; z < kTailMaxSplit; ++z)
       if (z < x.s) {
         a.x += v[z].x; a.y += v[z].y; a.z += v[z].z; a.w += v[z].w;
       }
+    return a;
+  };
+  if (batch_skewed(p.tile_off[p.G], mt_live, p.skew)) {   // tail_store_partial's layout: four rows of a column
+    const int c = threadIdx.x, col = nt * kTileN + c;
+    if (col >= p.N) return;
+#pragma unroll
+    for (int i = 0; i < kFixRows / 4; ++i) {
+      const int r = part * kFixRows + 4 * i;
+      if (row0 + r >= row_end) break;
+      const int e = ((r >> 5 & 3) * kTileTN + (c >> 5 & 1)) * 4 + (r >> 3 & 3);
+      const float4 a = sum((e * kTileThreads + ((r >> 7) * 4 + (c >> 6)) * kWave + 32 * (r >> 2 & 1) + (c & 31)) * 4);
+      const float v[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (row0 + r + u < row_end) p.out[static_cast<size_t>(row0 + r + u) * p.N + col] = f32_to_bf16(v[u]);
+    }
+    return;
+  }
+  const int c = (threadIdx.x & 63) * 4, col = nt * kTileN + c;
+  if (col >= p.N) return;
+#pragma unroll
+  for (int i = 0; i < kFixRows / 4; ++i) {
+    const int r = part * kFixRows + 4 * i + (threadIdx.x >> 6);
+    if (row0 + r >= row_end) break;
+    const float4 a = sum(r * kTileN + c);
     uint2 o;
     o.x = f32x2_to_bf16x2(a.x, a.y);
     o.y = f32x2_to_bf16x2(a.z, a.w);
@@ -356,7 +377,7 @@ hipError_t launch(int bm, bool packed, int grid, const BatchArgs& p, hipStream_t
 // rows 96 / 97 / 100, 200 rows 138 / 125 / 107.
 int batch_tile_rows(int T, int K, int pool, float peak) {
   const double avg = static_cast<double>(T) * K / pool;
-  if (avg <= 36) return 64;
+  if (avg <= 32) return 64;
   return (pool >= 32 ? avg <= 85 : avg * peak <= 104) ? 128 : 0;
 }
 
@@ -366,7 +387,19 @@ hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int 
   const int nonempty = static_cast<int>(std::min<int64_t>(TK, a.E));
   const int shared_tiles = a.n_shared * ((a.T + bm - 1) / bm);
   const int max_tiles = static_cast<int>(TK / bm) + nonempty + shared_tiles;
+  const int max_wide = static_cast<int>(TK / kTileM) + nonempty + a.n_shared * ((a.T + kTileM - 1) / kTileM);
   BatchArgs p{};
+  // The rule above knows the average and the prior, not the routing: tokens that all choose the same
+  // few experts make groups of many row tiles, and every one is another pass over its expert's weights.
+  // So the counts decide on the device: with more than skew / 8 row tiles for each 256-row one, the
+  // many-token path's GEMMs, launched beside these, do the work and these leave (batch_skewed).
+  // Mixtral-shaped, plain routing, every token to the same two experts, many-token path / 64- or 128-row
+  // tiles / this way: 144 tokens (3 tiles for 1) 206 / 266 / 196 us, 208 (2 for 1) 216 / 272 / 217, 400
+  // (4 for 2) 326 / 450 / 313; DeepSeek-shaped, to twelve experts, 333 tokens (5 for 2) 148 / 129 / 108,
+  // 900 193 / 225 / 183. The launch that leaves costs about 3 us; it is not made where no routing can be
+  // skewed: a group holds at most T rows.
+  p.skew = bm == 64 ? 20 : pool >= 32 ? 11 : 9;
+  const bool may_skew = 8 * ((std::min(a.T, kTileM) + bm - 1) / bm) > p.skew;
   p.row_tok = pb.row_tok;
   p.offsets = pb.offsets;
   p.tile_off = pb.tile_off;
@@ -392,6 +425,10 @@ hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int 
   }
   err = launch<0>(bm, a.packed, max_tiles * p.n_tiles, p, stream);
   if (err != hipSuccess) return err;
+  if (may_skew) {
+    err = launch_grouped_skewed(0, a, pb, max_wide, p.skew, H, O, part, lora, stream);
+    if (err != hipSuccess) return err;
+  }
   record_mark(marks, 0, stream);
   if (lora) {
     err = launch_lora_hidden(*lora, a, pb, bm, max_tiles, H, stream);
@@ -417,9 +454,12 @@ hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int 
   }
   err = launch<1>(bm, a.packed, max_tiles * p.n_tiles * p.split, p, stream);
   if (err != hipSuccess) return err;
+  if (may_skew) {
+    err = launch_grouped_skewed(1, a, pb, max_wide, p.skew, H, O, part, lora, stream);
+    if (err != hipSuccess) return err;
+  }
   if (sliced) {
-    const int64_t mt = TK / kTileM + nonempty + a.n_shared * ((a.T + kTileM - 1) / kTileM);   // the most tiles
-    const int tails = static_cast<int>(std::min<int64_t>((mt * wide_tiles + 7) / 8, kTailSlotsPerXcd));
+    const int tails = static_cast<int>(std::min<int64_t>((static_cast<int64_t>(max_wide) * wide_tiles + 7) / 8, kTailSlotsPerXcd));
     const int parts = (std::min(a.T, kTileM) + kFixRows - 1) / kFixRows;   // a group holds at most T rows
     hipLaunchKernelGGL(batch_fixup_kernel, dim3(8 * tails * parts), dim3(kThreads), 0, stream, p, parts);
     err = hipGetLastError();

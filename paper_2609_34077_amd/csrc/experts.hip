@@ -55,6 +55,8 @@ struct GemmArgs {
   int mt_max;               // bound on row tiles (the grid is sized for mt_max * n_tiles tiles)
   int n_tiles;              // column tiles
   int cu_xcd;               // workgroups an XCD runs at once (one per CU)
+  const int32_t* batch_off; // beside the batch path: its [G+1] tile offsets, and the launch runs only when
+  int skew;                 // they are skewed (batch_skewed); else null
 };
 
 __device__ __forceinline__ int find_group(const int32_t* tile_off, int G, int mt) {
@@ -161,6 +163,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void grouped_gemm_bf16(const GemmArgs
   // each XCD's workgroups that XCD's share of the live tiles (their count read on the device),
   // so every XCD gets an equal share however many tiles are live.
   const int mt_live = p.tile_off[p.G];
+  if (p.batch_off && !batch_skewed(p.batch_off[p.G], mt_live, p.skew)) return;
   const int live = mt_live * p.n_tiles;
   const int Kdim = EPI == 0 ? p.d : p.F;
   TileJob job;
@@ -882,57 +885,64 @@ hipError_t launch_combine_f32(const ExpertArgs& a, const PermBuffers& pb, const 
   return hipGetLastError();
 }
 
+// GEMM `epi` (0 gate/up into H, 1 down into O) over the row tiles of tile_off, at most max_tiles.
+static GemmArgs gemm_args(int epi, const ExpertArgs& a, const PermBuffers& pb, const int32_t* tile_off, int max_tiles,
+                          uint16_t* H, void* O, float* part, const LoraArgs* lora) {
+  GemmArgs g{};
+  g.row_tok = pb.row_tok;
+  g.offsets = pb.offsets;
+  g.tile_off = tile_off;
+  g.part = part;
+  g.cu_xcd = device_cus_per_xcd();
+  g.G = a.E + a.n_shared; g.E = a.E; g.F = a.F; g.d = a.d;
+  g.mt_max = max_tiles;
+  g.a = epi == 0 ? static_cast<const uint16_t*>(a.x) : H;
+  g.w = static_cast<const uint16_t*>(epi == 0 ? a.w_gate_up : a.w_down);
+  g.ws = static_cast<const uint16_t*>(epi == 0 ? a.ws_gate_up : a.ws_down);
+  g.out = epi == 0 ? H : O;
+  g.n_tiles = epi == 0 ? (a.F + BN / 2 - 1) / (BN / 2) : (a.d + BN - 1) / BN;
+  if (lora) {
+    g.lora_u = epi == 0 ? lora->u : lora->v;
+    g.lora_b = epi == 0 ? lora->bp_gate_up : lora->bp_down;
+  }
+  return g;
+}
+
+hipError_t launch_grouped_skewed(int epi, const ExpertArgs& a, const PermBuffers& pb, int max_tiles, int skew, uint16_t* H,
+                                 uint16_t* O, float* part, const LoraArgs* lora, hipStream_t stream) {
+  GemmArgs g = gemm_args(epi, a, pb, pb.wide_off, max_tiles, H, O, part, lora);
+  g.batch_off = pb.tile_off;
+  g.skew = skew;
+  const dim3 grid = grouped_grid(max_tiles, g.n_tiles);
+  if (epi == 0) launch_grouped<0>(lora != nullptr, a.packed, grid, g, stream);
+  else launch_grouped<1>(lora != nullptr, a.packed, grid, g, stream);
+  return hipGetLastError();
+}
+
 hipError_t launch_experts_bf16(const ExpertArgs& a, const PermBuffers& pb, uint16_t* H, float* O, float* part,
                                void* y, int max_tiles, hipStream_t stream, hipEvent_t* marks, uint16_t* ab,
                                const LoraArgs* lora) {
-  const int G = a.E + a.n_shared;
-  GemmArgs g{};
-  g.ab = ab;
-  g.part = part;
-  g.cu_xcd = device_cus_per_xcd();
-  const dim3 fixup_grid(8 * kTailSlotsPerXcd * kTailFixParts);
   hipError_t err;
   if (lora) {
     err = launch_lora_prepare(*lora, a, pb, kGemmBM, max_tiles, stream);
     if (err != hipSuccess) return err;
-    g.lora_u = lora->u;
-    g.lora_b = lora->bp_gate_up;
   }
-  g.row_tok = pb.row_tok;
-  g.offsets = pb.offsets;
-  g.tile_off = pb.tile_off;
-  g.G = G; g.E = a.E; g.F = a.F; g.d = a.d;
-  g.mt_max = max_tiles;
-
-  g.a = static_cast<const uint16_t*>(a.x);
-  g.w = static_cast<const uint16_t*>(a.w_gate_up);
-  g.ws = static_cast<const uint16_t*>(a.ws_gate_up);
-  g.out = H;
-  const int nt1 = (a.F + BN / 2 - 1) / (BN / 2);
-  g.n_tiles = nt1;
-  launch_grouped<0>(lora != nullptr, a.packed, grouped_grid(max_tiles, nt1), g, stream);
+  GemmArgs g = gemm_args(0, a, pb, pb.tile_off, max_tiles, H, O, part, lora);
+  g.ab = ab;
+  launch_grouped<0>(lora != nullptr, a.packed, grouped_grid(max_tiles, g.n_tiles), g, stream);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   record_mark(marks, 0, stream);
   if (lora) {
     err = launch_lora_hidden(*lora, a, pb, kGemmBM, max_tiles, H, stream);
     if (err != hipSuccess) return err;
-    g.lora_u = lora->v;
-    g.lora_b = lora->bp_down;
   }
-
-  g.ab = nullptr;
-  g.a = H;
-  g.w = static_cast<const uint16_t*>(a.w_down);
-  g.ws = static_cast<const uint16_t*>(a.ws_down);
-  g.out = O;
-  const int nt2 = (a.d + BN - 1) / BN;
-  g.n_tiles = nt2;
-  launch_grouped<1>(lora != nullptr, a.packed, grouped_grid(max_tiles, nt2), g, stream);
+  g = gemm_args(1, a, pb, pb.tile_off, max_tiles, H, O, part, lora);
+  launch_grouped<1>(lora != nullptr, a.packed, grouped_grid(max_tiles, g.n_tiles), g, stream);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   if (tail_can_split(1, a.F / BK)) {
-    hipLaunchKernelGGL(grouped_tail_fixup, fixup_grid, dim3(GEMM_THREADS), 0, stream, g);
+    hipLaunchKernelGGL(grouped_tail_fixup, dim3(8 * kTailSlotsPerXcd * kTailFixParts), dim3(GEMM_THREADS), 0, stream, g);
     err = hipGetLastError();
     if (err != hipSuccess) return err;
   }

@@ -384,6 +384,10 @@ __device__ __forceinline__ TileSlices tile_slices(int lid, int live, int cu_xcd,
   return {x.s, xcd * kTailSlotsPerXcd + t * x.s};
 }
 
+// The groups' rows are spread so unevenly that the many-token path's 256-row tiles are the faster ones
+// for a serving batch: its row tiles exceed skew / 8 of theirs (batch.hip).
+__device__ __forceinline__ bool batch_skewed(int tiles, int wide_tiles, int skew) { return 8 * tiles > skew * wide_tiles; }
+
 // Partial-tile slot layout: float4 e of thread tid at [e][tid] (coalesced for both sides).
 constexpr int kTailTileFloats = kTileM * kTileN;
 

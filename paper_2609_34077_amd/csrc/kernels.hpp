@@ -147,6 +147,11 @@ int decode_split(int T, int d, int F, int E, int K, int n_shared);
 int decode_split_gate_up(int T, int d, int F, int E, int K, int n_shared);
 hipError_t launch_experts_bf16_decode(const ExpertArgs& a, const PermBuffers& pb, uint16_t* H, float* P, float* O,
                                       void* y, hipStream_t stream, hipEvent_t* marks);
+// GEMM `epi` (0 gate/up, 1 down) of that path on pb.wide_off's tiles, beside a batch launch: runs only when
+// the batch path's tiles (pb.tile_off) are skewed (batch_skewed); the down GEMM's partial tiles are left to
+// the batch path's fix-up.
+hipError_t launch_grouped_skewed(int epi, const ExpertArgs& a, const PermBuffers& pb, int max_tiles, int skew, uint16_t* H,
+                                 uint16_t* O, float* part, const LoraArgs* lora, hipStream_t stream);
 // bf16, a serving-sized batch (batch.hip): few enough rows per expert that the weight stream bounds the
 // layer (with adapters for any number of tokens, else above kDecodeMaxT). batch_tile_rows: the row-tile size to permute
 // and launch with, 0 when the many-token path is faster; pool: experts the routing can select,

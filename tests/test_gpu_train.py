@@ -128,20 +128,27 @@ def _layer(cfg):
 # slices. Both model shapes at serving sizes, and rounds of every kind: one short round in 8, 4 and 2
 # slices, XCDs with and without slices (132 tiles), a full round behind the split one (264 tiles), an odd
 # number of 64-column chunks, more tokens than a 256-row tile in the shared group, experts that the
-# routing leaves out (fewer tiles, more slices than expected).
-@pytest.mark.parametrize("T,d,F,E,K,ns,mode,kept", [
-    (96, 4096, 14336, 8, 2, 0, L.ROUTE_SOFT_PRIOR, (0, 2, 5, 7)),
-    (208, 4096, 14336, 8, 2, 0, L.ROUTE_HARD_MASK, (0, 2, 5, 7)),
-    (333, 2048, 1408, 64, 6, 2, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),
-    (96, 1088, 2048, 8, 2, 0, L.ROUTE_PLAIN, ()),
-    (130, 1024, 4096, 8, 2, 1, L.ROUTE_PLAIN, ()),
-    (40, 4096, 4096, 8, 2, 0, L.ROUTE_SOFT_PRIOR, (1, 4)),
-    (300, 1024, 2048, 33, 1, 0, L.ROUTE_PLAIN, ()),
-    (512, 1024, 2048, 66, 1, 0, L.ROUTE_PLAIN, ()),
-    (600, 320, 2112, 64, 2, 1, L.ROUTE_PLAIN, ()),
-    (600, 320, 4096, 40, 2, 1, L.ROUTE_PLAIN, ()),
+# routing leaves out (fewer tiles, more slices than expected). `hot`: tokens that all lean towards these
+# experts, for which a batch leaves its small tiles; at the last counts that keep them too.
+@pytest.mark.parametrize("T,d,F,E,K,ns,mode,kept,hot", [
+    (96, 4096, 14336, 8, 2, 0, L.ROUTE_SOFT_PRIOR, (0, 2, 5, 7), ()),
+    (208, 4096, 14336, 8, 2, 0, L.ROUTE_HARD_MASK, (0, 2, 5, 7), ()),
+    (333, 2048, 1408, 64, 6, 2, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set()), ()),
+    (96, 1088, 2048, 8, 2, 0, L.ROUTE_PLAIN, (), ()),
+    (130, 1024, 4096, 8, 2, 1, L.ROUTE_PLAIN, (), ()),
+    (40, 4096, 4096, 8, 2, 0, L.ROUTE_SOFT_PRIOR, (1, 4), ()),
+    (300, 1024, 2048, 33, 1, 0, L.ROUTE_PLAIN, (), ()),
+    (512, 1024, 2048, 66, 1, 0, L.ROUTE_PLAIN, (), ()),
+    (600, 320, 2112, 64, 2, 1, L.ROUTE_PLAIN, (), ()),
+    (600, 320, 4096, 40, 2, 1, L.ROUTE_PLAIN, (), ()),
+    (128, 1024, 4096, 8, 2, 0, L.ROUTE_PLAIN, (), (1, 4)),
+    (129, 1024, 4096, 8, 2, 0, L.ROUTE_PLAIN, (), (1, 4)),
+    (400, 1088, 2048, 8, 2, 0, L.ROUTE_PLAIN, (), (1, 4)),
+    (256, 1024, 2048, 8, 1, 1, L.ROUTE_PLAIN, (), (3,)),
+    (140, 512, 2048, 40, 6, 2, L.ROUTE_PLAIN, (), (3, 5, 11, 20, 21, 39)),
+    (333, 512, 1408, 64, 6, 2, L.ROUTE_PLAIN, (), tuple(synth.deepseek_mask_set())),
 ])
-def test_forward_train_same_bits(T, d, F, E, K, ns, mode, kept):
+def test_forward_train_same_bits(T, d, F, E, K, ns, mode, kept, hot):
     U.say(f"forward and training forward T={T} d={d} F={F} E={E} K={K} shared={ns} mode={mode}")
     g = torch.Generator(device="cuda")
     g.manual_seed(T + d)
@@ -153,6 +160,9 @@ def test_forward_train_same_bits(T, d, F, E, K, ns, mode, kept):
     prior = synth.concentrated_prior(E, kept, 20.0 if len(kept) == 2 else 1.0) if mode == L.ROUTE_SOFT_PRIOR else None
     gate_mode = L.GATE_P if ns else L.GATE_RENORM
     x, wr = rand((T, d), 1.0), rand((E, d), 0.02)
+    if hot:
+        u = wr[list(hot)].float().sum(0)
+        x = (x.float() + 40.0 * u / u.norm()).bfloat16()
     gu, dn = rand((E, 2 * F, d), d ** -0.5), rand((E, d, F), F ** -0.5)
     sh = dict(ws_gate_up=rand((ns, 2 * F, d), d ** -0.5), ws_down=rand((ns, d, F), F ** -0.5)) if ns else {}
     kw = dict(mask=mask, prior=prior, **sh)
@@ -160,6 +170,7 @@ def test_forward_train_same_bits(T, d, F, E, K, ns, mode, kept):
     idx1, gate1 = torch.empty_like(idx), torch.empty_like(gate)
     y = L.maskmoe_layer_forward(x, wr, gu, dn, K, mode, gate_mode, topk_idx=idx1, topk_gate=gate1, **kw)
     torch.cuda.synchronize()
+    assert not hot or set(idx.flatten().tolist()) <= set(hot)
     assert torch.equal(idx, idx1) and torch.equal(gate, gate1)
     assert torch.equal(y, y_train)
     if d % 128 == 0:
