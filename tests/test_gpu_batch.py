@@ -36,6 +36,11 @@ CASES = [
     _cfg(906, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),   # the last, many experts
     _cfg(597, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),
     _cfg(40, 256, 16, 8, 192, 64),                                    # the most experts and shared experts
+    # model widths (many chunks, several column tiles, a down reduction in slices): the last batch of
+    # 64-row tiles, the first of 128-row ones
+    _cfg(128, 8, 2, 0, 1152, 2048),
+    _cfg(129, 8, 2, 1, 1152, 2048),
+    _cfg(100, 16, 2, 0, 1088, 2112, L.ROUTE_SOFT_PRIOR, KEEP4),
     # twelve experts take every token: more row tiles than the batch path keeps, so that the many-token
     # path's tiles run beside it
     _cfg(333, 64, 6, 2, 256, 2048, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())).with_(delta=25.0),
@@ -56,13 +61,23 @@ def test_batch_packed(cfg):
 # the adapters' chunk in front of the weight chunks: 64- and 128-row tiles, a split reduction (only
 # its first slice takes the adapters), ragged weight rows, one token
 @pytest.mark.parametrize("T,E,K,ns,d,F,rank", [(1, 8, 2, 1, 64, 64, 8), (17, 8, 2, 0, 128, 2048, 16), (129, 8, 2, 1, 192, 320, 4),
-                                               (300, 64, 6, 2, 256, 192, 8)])
+                                               (300, 64, 6, 2, 256, 192, 8), (100, 8, 2, 0, 1152, 2048, 8),
+                                               (130, 8, 2, 1, 1088, 2048, 5)])
 def test_batch_lora(T, E, K, ns, d, F, rank):
     check_lora(_cfg(T, E, K, ns, d, F), rank=rank)
 
 
 def test_batch_lora_skewed():
     check_lora(_cfg(333, 64, 6, 2, 256, 2048, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())).with_(delta=25.0), rank=8)
+
+
+# The serving batches of both model shapes, on tokens of every row tile.
+@pytest.mark.parametrize("T,E,K,ns,d,F,mode,keep,packed", [
+    (96, 8, 2, 0, 4096, 14336, L.ROUTE_SOFT_PRIOR, KEEP4, True),
+    (333, 64, 6, 2, 2048, 1408, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set()), False),
+])
+def test_batch_model_shapes(T, E, K, ns, d, F, mode, keep, packed):
+    check_layer(_cfg(T, E, K, ns, d, F, mode, keep), sample=True, packed=packed)
 
 
 # the many-token path's last tile of a group: 64, 128, 192 or 256 rows multiplied. Two experts take
