@@ -1200,14 +1200,12 @@ hipError_t launch_route(bool bf16, const void* x, const void* w_router, int T, i
       const bool small = T <= 128;
       if (split) {   // T >= kRouteSplitMinT
         if (need <= 16) err = launch_bf16<1, 1, 1, 8, false, true>(p, stream);
-        else if (need <= 64) err = launch_bf16<1, 4, 1, 16, false, true>(p, stream);
+        else if (need <= 64) err = launch_bf16<1, 4, 1, 8, false, true>(p, stream);
         else err = launch_bf16<2, 4, 4, 1, false, true>(p, stream);
       } else if (need <= 16) {   // the split launch's logit tiles for many tokens: the same bits
         err = small ? launch_bf16<1, 1, 1, 16>(p, stream) : launch_bf16<1, 1, 1, 8>(p, stream);
       } else if (need <= 64) {
-        // 16 wavefronts: a wavefront's whole share of d = 2048 is one group of loads, and each selects one
-        // token (8 wavefronts: two of each; DeepSeek-shaped, 333 tokens 21.2 -> 19.4 us)
-        err = launch_bf16<1, 4, 1, 16>(p, stream);
+        err = launch_bf16<1, 4, 1, 8>(p, stream);
       } else {
         err = small ? launch_bf16<1, 4, 4, 2>(p, stream) : launch_bf16<2, 4, 4, 1>(p, stream);
       }
@@ -1245,7 +1243,7 @@ hipError_t launch_route_permute(const void* x, const void* w_router, int T, int 
   p.n_shared = n_shared;
   p.tile_rows = tile_rows;
   if (E <= 16) return launch_bf16<1, 1, 1, 16, true>(p, stream);
-  if (E <= 64) return launch_bf16<1, 4, 1, 16, true>(p, stream);
+  if (E <= 64) return launch_bf16<1, 4, 1, 8, true>(p, stream);
   return launch_bf16<1, 4, 4, 2, true>(p, stream);
 }
 
