@@ -16,9 +16,9 @@
 // and the WK partial tiles are summed in LDS in a fixed order. Small token counts
 // (decode) use WK = 8..16 so all of d is in flight at once; large token counts stream x.
 // Many tokens routed through many layers at once use tiles staged through LDS instead
-// (route_mid_kernel, route_gemm_kernel, route_tile_kernel).
+// (route_mid_kernel, route_gemm_kernel, route_wide_kernel, route_tile_kernel).
 // The selection reads the fp32 logits from LDS: up to 16 experts one 16-lane row per token (one layer)
-// or one thread per (token, layer), above that one wavefront per pair.
+// or one thread per (token, layer), above that one wavefront per pair where few share it (wave_selects).
 
 #include <limits.h>
 #include <math.h>
@@ -45,19 +45,23 @@ constexpr int kMaxModeParams = 512;
 // lanes took ~5 us of the 4096-token selection kernel), the per-thread selection replays the
 // same tree, so every path gives the same bits.
 constexpr int kSelThreadE = 16;
-// More than 64 experts are routed in one launch with selection; the tiled router GEMM pays off there
-// once a launch has many tokens and enough router outputs to fill half its 256-wide tile.
-constexpr int kRouteGemmMinT = 1024;
-constexpr int kRouteGemmMinOutputs = 128;
-// Launches of the tile kernels (route_mid_kernel, route_gemm_kernel, route_tile_kernel): they all sum
-// a logit over the 64-wide k-tiles in the same order, so that split and fused routing of the same
-// call give the same bits whichever of them each takes. Their 32-bit offsets reach over a tile's rows.
+// Launches that the tile kernels (route_mid_kernel, route_gemm_kernel, route_wide_kernel,
+// route_tile_kernel) can take: they all sum a logit in ascending order of k, as the 32-token tiles of
+// route_bf16_kernel do, so that split and fused routing of the same call give the same bits whichever of
+// them each takes. Their 32-bit offsets reach over a tile's rows.
 inline bool route_tiles(int T, int d, int E, int L) {
-  const int outs = L * E;
-  if (d % 64 != 0 || d > (1 << 20) || T < kRouteSplitMinT) return false;
-  if (E > kRouteSplitMaxE) return T >= kRouteGemmMinT && outs >= kRouteGemmMinOutputs;
-  return outs > 64;
+  return d % 64 == 0 && d <= (1 << 20) && T >= kRouteSplitMinT && L * E > 64;
 }
+// Of these, launches with selection that take the 32-token tiles of route_bf16_kernel (`groups` of
+// outputs): until they are more than one per CU, or two where short rows or many experts make the selection
+// the longer part, they hide it better than the tile GEMMs. 9 and 32 layers of 8 experts, d 4096, 32-token
+// tiles / tile GEMM: 600 tokens 54 / 64 and 100 / 130 us, 8192 tokens 55 / 65 and 103 / 132, 12000 tokens
+// 101 / 66 and 187 / 134; 13 layers of 5 experts, d 1024, 16000 tokens 31 / 38, 33000 66 / 45; one layer of
+// 100 experts, d 2048, 9000 tokens 137 / 155, 40000 251 / 177; of 256, 8192 tokens 171 / 384.
+inline bool route_small_tiles(int T, int d, int E, int groups) {
+  return (T + 31) / 32 * groups <= (d < 2048 || E > kWave ? 512 : 256);
+}
+constexpr int kRouteWideT = 32768;
 
 struct RouteParams {
   const void* x;
@@ -339,7 +343,7 @@ __global__ __launch_bounds__(kSelThreads) void route_select_wave_kernel(const Ro
 // (largest key, then lowest index), and the softmax normaliser is summed in expert order
 // (selection order for the renormalised rule), as in route_finalize, so both give the same bits.
 // A thread per pair leaves most of a 16-token tile's threads idle behind K + 1 serial passes
-// over E keys: 333 tokens, 64 experts, top-6: 57 us, this way 20. The selections are also left in
+// over E keys: 333 tokens, 64 experts, top-6: 57 us, this way 20 (with many pairs: wave_selects). The selections are also left in
 // sel_lds [T, K] for the permutation when given (one layer).
 __device__ void route_finalize_wave(const RouteParams& p, const float* logits, int ld, const float* lo, int t0, int TT,
                                     int lg0, int nl, int32_t* sel_lds, int nwaves) {
@@ -444,6 +448,20 @@ __device__ void route_finalize_wave(const RouteParams& p, const float* logits, i
     if (p.logits)
       for (int e = lane; e < E; e += 64) p.logits[obase * E + e] = z[e];
   }
+}
+
+// Whether route_finalize_wave selects a workgroup's `pairs` pairs sooner than route_finalize (a thread per
+// pair), in key comparisons of the latter (about 0.13 us each: a thread walks E keys K + 1 times): a
+// wavefront's pair costs about 38 of them with up to 64 experts, top-6, 121 with 256, top-8. Workgroups of
+// four wavefronts and 32 tokens, 600 tokens, a thread / a wavefront per pair: 24 experts, top-4, 6 layers
+// 46 / 207 us; 64 experts, top-6, 4 layers 96 / 167; 256 experts, top-8, one layer 391 / 165. With more
+// workgroups than CUs the threads' waits overlap and the wavefronts' work does not: 24 experts, one layer,
+// 16000 tokens 39 / 50.
+__device__ __forceinline__ bool wave_selects(int E, int K, int pairs, int nthreads) {
+  if (gridDim.x * gridDim.y > 256) return false;
+  const int nwaves = nthreads / kWave;
+  const int wave_cost = 4 * (K + 1) + (E <= kWave ? 10 : E / 3);
+  return (pairs + nwaves - 1) / nwaves * wave_cost < (pairs + nthreads - 1) / nthreads * (K + 1) * E;
 }
 
 // fmaxf over the 16 lanes of the row, in every lane. fmaxf drops NaN operands, so any order
@@ -703,9 +721,9 @@ __global__ __launch_bounds__(64 * WN * WK) void route_bf16_kernel(const RoutePar
     } else {
       permute_block<1>(sel_lds, p.T, p.K, p.E, p.n_shared, p.tile_rows, p.pb, plds, NT);
     }
-  } else if (p.E > kSelThreadE) {
+  } else if (p.E > kSelThreadE && wave_selects(p.E, p.K, TT * nl, NT)) {
     route_finalize_wave(p, red, NO, lo, t0, TT, lg0, nl, nullptr, NT / 64);
-  } else if (TT == 16 && NT >= 4 * 64 && nl == 1) {   // one layer: four tokens per wavefront
+  } else if (TT == 16 && NT >= 4 * 64 && nl == 1 && p.E <= kSelThreadE) {   // one layer: four tokens per wavefront
     __shared__ float sc[16 * 16];
     route_select_rows(p, red, NO, lo, sc, t0, static_cast<size_t>(lg0) * p.T + t0, nullptr);
   } else {
@@ -876,6 +894,138 @@ __global__ __launch_bounds__(kRgThreads, 2) void route_gemm_kernel(const RoutePa
           for (int r = 0; r < 16; ++r)
             logits[(i * 32 + (lane & 31)) * LD + wn * (BN / 2) + j * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)] =
                 acc[j][i][r];
+    }
+    lds_sync();
+    route_finalize<true>(p, logits, LD, lo, t0 + h * HALF, HALF, lg0, nl, NT);
+    lds_sync();   // the next phase overwrites the logits
+  }
+}
+
+// Selection with the logits, more than 128 outputs and more than kRouteWideT tokens: 256 tokens x 256
+// outputs per workgroup of eight wavefronts, double-buffered k-tiles, one workgroup per CU; the selection
+// as in route_gemm_kernel, on 128 tokens at a time. (32 layers of 8 experts, d 4096, 128-token tiles /
+// this: 20000 tokens 137 / 143 us, 33000 181 / 157, 64000 215 / 192.)
+constexpr int kRwBM = 256, kRwThreads = 512;
+
+__global__ __launch_bounds__(kRwThreads) void route_wide_kernel(const RouteParams p) {
+  constexpr int BM = kRwBM, BN = kRgMaxBN, BK = kRgBK, NT = kRwThreads;
+  constexpr int WN = 4;                        // waves: 2 along tokens x 4 along outputs
+  constexpr int TM = 4, TN = 2;                // 32x32 fragments per wave: 128 tokens x 64 outputs
+  constexpr int HALF = BM / 2;                 // token rows per selection phase (one wave row)
+  constexpr int UA = BM * 8 / NT, UB = BN * 8 / NT;   // 16-byte units per thread and stage
+  constexpr int SA = BM * 8, SB = BN * 8;             // 16-byte slots per stage
+  constexpr int STAGING = 2 * (SA + SB) * 16;
+  constexpr int LD = BN + 1;                   // logits row stride: odd, so token rows fall on distinct banks
+  constexpr int LOGITS = HALF * LD * 4;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[STAGING > LOGITS ? STAGING : LOGITS];
+  __shared__ float lo[BN];
+  u32x4* lds_a = reinterpret_cast<u32x4*>(smem);   // [2][SA]
+  u32x4* lds_b = lds_a + 2 * SA;                    // [2][SB]
+  float* logits = reinterpret_cast<float*>(smem);   // [HALF][LD], after the k-loop
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / WN, wn = wave % WN;
+  const int t0 = blockIdx.x * BM;
+  const int lg0 = blockIdx.y * p.lpw;
+  const int nl = min(p.lpw, p.L - lg0);
+  const int nout = nl * p.E;
+  const uint16_t* x = static_cast<const uint16_t*>(p.x);
+  const uint16_t* w = static_cast<const uint16_t*>(p.w) + static_cast<size_t>(lg0) * p.E * p.d;
+
+  // Thread tid loads rows (tid >> 3) + 64 i of each operand; rows past the last token or
+  // output are clamped onto valid rows and their results never written.
+  const int r0 = tid >> 3;
+  const int chunk = ((tid & 7) ^ lds_swizzle(r0)) * 8;
+  const uint16_t* asrc[UA];
+  const uint16_t* bsrc[UB];
+#pragma unroll
+  for (int i = 0; i < UA; ++i) asrc[i] = x + static_cast<size_t>(min(t0 + r0 + 64 * i, p.T - 1)) * p.d + chunk;
+#pragma unroll
+  for (int i = 0; i < UB; ++i) bsrc[i] = w + static_cast<size_t>(min(r0 + 64 * i, nout - 1)) * p.d + chunk;
+  int aoff[TM], boff[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) aoff[i] = (wm * 128 + i * 32 + (lane & 31)) * 8;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) boff[j] = (wn * 64 + j * 32 + (lane & 31)) * 8;
+  const int sw = lds_swizzle(lane);   // fragment rows are a multiple of 32 plus (lane & 31)
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+  u32x4 ra[UA], rb[UB];
+  auto gload = [&](int kt) {
+#pragma unroll
+    for (int i = 0; i < UA; ++i) ra[i] = *reinterpret_cast<const u32x4*>(asrc[i] + kt * BK);
+#pragma unroll
+    for (int i = 0; i < UB; ++i) rb[i] = *reinterpret_cast<const u32x4*>(bsrc[i] + kt * BK);
+  };
+  auto lstore = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < UA; ++i) lds_a[buf * SA + tid + NT * i] = ra[i];
+#pragma unroll
+    for (int i = 0; i < UB; ++i) lds_b[buf * SB + tid + NT * i] = rb[i];
+  };
+  u32x4 af[2][TM], bf[2][TN];
+  auto read_frags = [&](int buf, int kk, int slot) {
+    const int ch = (kk * 2 + (lane >> 5)) ^ sw;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) af[slot][i] = lds_a[buf * SA + aoff[i] + ch];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bf[slot][j] = lds_b[buf * SB + boff[j] + ch];
+  };
+
+  // k-tile kt sits in LDS buffer kt & 1 and tile kt + 1 in registers; after the first k16 step
+  // of tile kt the registers go to the other buffer and are refilled with tile kt + 2.
+  // Branch-free body, interleaved by LLVM's MFMA/DS strategy as in the expert GEMM: past the end
+  // the last tile is loaded again into the idle buffer, which nothing reads.
+  const int nk = p.d / BK;
+  gload(0);
+  lstore(0);
+  gload(min(1, nk - 1));
+  __syncthreads();
+  read_frags(0, 0, 0);
+  for (int kt = 0; kt < nk; ++kt) {
+    const int buf = kt & 1;
+    __builtin_amdgcn_iglp_opt(0);
+#pragma unroll
+    for (int kk = 0; kk < BK / 16; ++kk) {
+      const int cur = kk & 1;
+      if (kk + 1 < BK / 16) read_frags(buf, kk + 1, cur ^ 1);
+      if (kk == 0) {
+        lstore(buf ^ 1);
+        gload(min(kt + 2, nk - 1));
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_32x32x16(af[cur][i], bf[cur][j], acc[i][j]);
+    }
+    __syncthreads();
+    read_frags(buf ^ 1, 0, 0);
+  }
+
+  // The last barrier of the loop ends every read of the staging buffers. Phase h: the waves
+  // of token half h write their logits, then every thread selects for those tokens.
+  // acc[i][j][4 jj + ii] is token row wm*128 + i*32 + 8 jj + 4 (lane >> 5) + ii, output
+  // column wn*64 + j*32 + (lane & 31).
+  for (int i = tid; i < nout; i += NT) lo[i] = key_offset(p.mode, p.modep[lg0 * p.E + i]);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (wm == h) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int row = i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            logits[row * LD + wn * 64 + j * 32 + (lane & 31)] = acc[i][j][r];
+          }
     }
     lds_sync();
     route_finalize<true>(p, logits, LD, lo, t0 + h * HALF, HALF, lg0, nl, NT);
@@ -1101,7 +1251,8 @@ __global__ __launch_bounds__(64 * kF32Waves) void route_f32_kernel(const RoutePa
     }
   }
   lds_sync();
-  if (p.E > kSelThreadE) route_finalize_wave(p, logits, ld, lo, t0, kF32TT, lg0, nl, nullptr, kF32Waves);
+  if (p.E > kSelThreadE && wave_selects(p.E, p.K, kF32TT * nl, NT))
+    route_finalize_wave(p, logits, ld, lo, t0, kF32TT, lg0, nl, nullptr, kF32Waves);
   else route_finalize(p, logits, ld, lo, t0, kF32TT, lg0, nl, NT);
 }
 
@@ -1171,28 +1322,32 @@ hipError_t launch_route(bool bf16, const void* x, const void* w_router, int T, i
       // 128-output tiles of 64 / 128 tokens 82 / 77, 131072 tokens 310 / 293 (262 non-temporal).
       const int outs = p.L * E;
       const int mt = (T + kRmBM - 1) / kRmBM;
-      auto cover = [&](int bn) {   // whole layers per workgroup; column blocks
-        p.lpw = std::max(std::min(bn / E, p.L), 1);
-        return (p.L + p.lpw - 1) / p.lpw;
-      };
-      if (outs <= 64 || mt * cover(64) <= 256) {
+      auto layers = [&](int bn) { return std::max(std::min(bn / E, p.L), 1); };   // whole layers per workgroup
+      auto cover = [&](int bn) { return (p.L + layers(bn) - 1) / layers(bn); };     // column blocks
+      if (mt * cover(64) <= 256) {
+        p.lpw = layers(64);
         hipLaunchKernelGGL(route_mid_kernel<64>, dim3(mt, cover(64)), dim3(kRmThreads), 0, stream, p);
       } else if (mt * cover(128) <= 512) {
+        p.lpw = layers(128);
         hipLaunchKernelGGL(route_mid_kernel<128>, dim3(mt, cover(128)), dim3(kRmThreads), 0, stream, p);
       } else if (outs <= 128) {
+        p.lpw = layers(128);
         hipLaunchKernelGGL((route_gemm_kernel<128, true>), dim3((T + kRgBM - 1) / kRgBM, cover(128)), dim3(kRgThreads),
                            0, stream, p);
       } else {
+        p.lpw = layers(256);
         hipLaunchKernelGGL(route_tile_kernel, dim3((T + kTileN - 1) / kTileN, cover(256)), dim3(kTileThreads), 0,
                            stream, p);
       }
       err = hipGetLastError();
-    } else if (route_tiles(T, d, E, p.L)) {
+    } else if (!split && route_tiles(T, d, E, p.L) && !route_small_tiles(T, d, E, (p.L + 256 / E - 1) / (256 / E))) {
       const bool narrow = p.L * E <= 128;   // one 128-output tile holds every layer
-      p.lpw = (narrow ? 128 : kRgMaxBN) / E;
-      if (p.lpw > p.L) p.lpw = p.L;
-      dim3 grid((T + kRgBM - 1) / kRgBM, (p.L + p.lpw - 1) / p.lpw);
+      const bool wide = !narrow && T > kRouteWideT;
+      p.lpw = std::min((narrow ? 128 : kRgMaxBN) / E, p.L);
+      const int bm = wide ? kRwBM : kRgBM;
+      const dim3 grid((T + bm - 1) / bm, (p.L + p.lpw - 1) / p.lpw);
       if (narrow) hipLaunchKernelGGL((route_gemm_kernel<128, false>), grid, dim3(kRgThreads), 0, stream, p);
+      else if (wide) hipLaunchKernelGGL(route_wide_kernel, grid, dim3(kRwThreads), 0, stream, p);
       else hipLaunchKernelGGL((route_gemm_kernel<kRgMaxBN, false>), grid, dim3(kRgThreads), 0, stream, p);
       err = hipGetLastError();
     } else {

@@ -205,6 +205,17 @@ SPLIT_CASES = [
     (17000, 320, 8, 2, 32, L.ROUTE_SOFT_PRIOR, L.GATE_RENORM),
     (17001, 64, 5, 3, 37, L.ROUTE_PLAIN, L.GATE_P),
     (600, 128, 16, 4, 5, L.ROUTE_HARD_MASK, L.GATE_P),
+    # without a workspace: the last batch of the 32-token tiles and the first of the 128-token ones (72 and
+    # 192 outputs), 256-token tiles, a thread or a wavefront per pair of more than 16 experts
+    (8192, 2048, 8, 2, 9, L.ROUTE_PLAIN, L.GATE_RENORM),
+    (8193, 2048, 8, 2, 9, L.ROUTE_PLAIN, L.GATE_RENORM),
+    (8193, 2048, 24, 4, 8, L.ROUTE_PLAIN, L.GATE_P),
+    (16385, 64, 5, 2, 13, L.ROUTE_SOFT_PRIOR, L.GATE_P),
+    (32769, 64, 8, 2, 17, L.ROUTE_PLAIN, L.GATE_RENORM),
+    (600, 64, 24, 4, 6, L.ROUTE_SOFT_PRIOR, L.GATE_P),
+    (4097, 64, 24, 4, 1, L.ROUTE_SOFT_PRIOR, L.GATE_P),
+    (4096, 64, 17, 1, 1, L.ROUTE_PLAIN, L.GATE_P),
+    (700, 64, 64, 6, 2, L.ROUTE_PLAIN, L.GATE_P),
 ]
 
 
@@ -234,6 +245,26 @@ def test_split_routing_matches_fused_bitwise(T, d, E, K, Lyr, mode, gate_mode):
     z = ws.view(torch.float32).view(Lyr, T, E).cpu().double().numpy()
     zr = np.stack([R.router_logits(U.f64(x, "bf16")[:64], U.f64(w, "bf16").reshape(Lyr, E, d)[l]) for l in range(Lyr)])
     np.testing.assert_allclose(z[:, :64], zr, rtol=1e-4, atol=1e-4 * np.abs(zr).max())
+
+
+# More than 64 experts (always one launch): every size of tile and form of selection gives a token the
+# same bits, in chunks of 600 tokens, of 9000 and all at once.
+@pytest.mark.parametrize("E,K,Lyr", [(72, 4, 1), (100, 8, 2), (256, 8, 1)])
+def test_many_expert_routing_is_independent_of_batch(E, K, Lyr):
+    T, d = 34000, 64
+    U.say(f"route many experts T={T} E={E} K={K} L={Lyr}")
+    x, w = _inputs(T, d, E, "bf16", 7100 + E, Lyr=Lyr)
+    xd, wd = U.dev(x), U.dev(w).view(Lyr, E, d)
+    whole = L.maskmoe_route(xd, wd, K, L.ROUTE_PLAIN, L.GATE_P)
+    for n in (600, 9000):
+        part = [L.maskmoe_route(xd[i:i + n], wd, K, L.ROUTE_PLAIN, L.GATE_P) for i in range(0, 18000, n)]
+        torch.cuda.synchronize()
+        for a, b in zip(whole, zip(*part)):
+            b = torch.cat(b, 1)
+            assert torch.equal(a[:, :b.shape[1]], b)
+    z = R.router_logits(U.f64(x, "bf16")[-64:], U.f64(w, "bf16").reshape(Lyr, E, d)[0])
+    U.check_routing(z, whole[0][0, -64:].cpu().numpy(), whole[1][0, -64:].cpu().numpy(),
+                    whole[2][0, -64:].cpu().numpy(), K, L.ROUTE_PLAIN, L.GATE_P)
 
 
 def test_split_routing_non_finite_logits_match_fused():
