@@ -131,7 +131,8 @@ int device_cus_per_xcd();
 constexpr int kTailSlots = 256;
 constexpr size_t kTailPartBytes = static_cast<size_t>(kTailSlots) * 256 * 256 * 4;
 
-// bf16, T > kDecodeMaxT (any T when training or with adapters): H = SwiGLU(X_g W_gate,up^T)
+// bf16, the many-token path: T > kDecodeMaxT (any T when training or with adapters) where the batch
+// path (batch_tile_rows) does not take the layer: H = SwiGLU(X_g W_gate,up^T)
 // per group; O = H W_down^T; y = combine. ab (training): the gate and up pre-activations,
 // bf16 [rows, 2F]. lora: the experts' low-rank adapters, added inside both GEMMs.
 // part: kTailPartBytes of workspace for the split tail tiles.

@@ -146,7 +146,7 @@ struct PrepareArgs {
   LoraArgs l;
   const uint16_t* x;
   PermBuffers pb;
-  int T, d, F, E, G, tile_rows, u_blocks;
+  int d, F, E, G, tile_rows, u_blocks;
   int gu_blocks, dn_blocks;   // packing workgroups of one expert's gate/up and down adapters
   bool whole;
 };
@@ -186,7 +186,7 @@ PrepareArgs prepare_args(const LoraArgs& l, const ExpertArgs& a, const PermBuffe
   p.l = l;
   p.x = static_cast<const uint16_t*>(a.x);
   p.pb = pb;
-  p.T = a.T; p.d = a.d; p.F = a.F; p.E = a.E; p.G = a.E + a.n_shared;
+  p.d = a.d; p.F = a.F; p.E = a.E; p.G = a.E + a.n_shared;
   p.tile_rows = tile_rows;
   p.u_blocks = tile_rows / kLoraRows * max_tiles;
   constexpr int kItems = kPackPer * kLoraThreads;
