@@ -377,7 +377,7 @@ hipError_t launch(int bm, bool packed, int grid, const BatchArgs& p, hipStream_t
 // rows 96 / 97 / 100, 200 rows 138 / 125 / 107.
 int batch_tile_rows(int T, int K, int pool, float peak) {
   const double avg = static_cast<double>(T) * K / pool;
-  if (avg <= 32) return 64;
+  if (avg <= 36) return 64;
   return (pool >= 32 ? avg <= 85 : avg * peak <= 104) ? 128 : 0;
 }
 
@@ -393,13 +393,15 @@ hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int 
   // few experts make groups of many row tiles, and every one is another pass over its expert's weights.
   // So the counts decide on the device: with more than skew / 8 row tiles for each 256-row one, the
   // many-token path's GEMMs, launched beside these, do the work and these leave (batch_skewed).
-  // Mixtral-shaped, plain routing, every token to the same two experts, many-token path / 64- or 128-row
-  // tiles / this way: 144 tokens (3 tiles for 1) 206 / 266 / 196 us, 208 (2 for 1) 216 / 272 / 217, 400
-  // (4 for 2) 326 / 450 / 313; DeepSeek-shaped, to twelve experts, 333 tokens (5 for 2) 148 / 129 / 108,
-  // 900 193 / 225 / 183. The launch that leaves costs about 3 us; it is not made where no routing can be
-  // skewed: a group holds at most T rows.
-  p.skew = bm == 64 ? 20 : pool >= 32 ? 11 : 9;
-  const bool may_skew = 8 * ((std::min(a.T, kTileM) + bm - 1) / bm) > p.skew;
+  // Mixtral-shaped, plain routing, every token to the same two experts, many-token path before its tail
+  // pieces / 64- or 128-row tiles / this way: 144 tokens (3 tiles for 1) 206 / 266 / 196 us, 208 (2 for
+  // 1) 216 / 272 / 217, 400 (4 for 2) 326 / 450 / 313; DeepSeek-shaped, to twelve experts, 333 tokens (5
+  // for 2) 148 / 129 / 108, 900 193 / 225 / 183. The launches that leave cost a layer about 4 us (333
+  // tokens 247 -> 251). Not made up to 128 tokens, where a group is at most two tiles of 64 rows (120
+  // tokens to the same two experts 217 / 220).
+  p.skew = bm == 64 ? 15 : pool >= 32 ? 11 : 9;
+  const bool may_skew = a.T > 128;
+  if (!may_skew) p.skew = 1 << 16;
   p.row_tok = pb.row_tok;
   p.offsets = pb.offsets;
   p.tile_off = pb.tile_off;

@@ -837,9 +837,9 @@ int device_cus_per_xcd() {
   return cu / 8;
 }
 
-// Grid of a grouped GEMM: 8 XCDs x (their largest share of tiles + tail slices).
-static dim3 grouped_grid(int max_tiles, int n_tiles) {
-  const long per_xcd = (static_cast<long>(max_tiles) * n_tiles + 7) / 8 + kTailSlotsPerXcd;
+// Grid of a grouped GEMM: 8 XCDs x (their largest share of tiles + tail slices where it has any).
+static dim3 grouped_grid(int max_tiles, int n_tiles, bool tails) {
+  const long per_xcd = (static_cast<long>(max_tiles) * n_tiles + 7) / 8 + (tails ? kTailSlotsPerXcd : 0);
   return dim3(static_cast<unsigned>(8 * per_xcd));
 }
 
@@ -913,7 +913,7 @@ hipError_t launch_grouped_skewed(int epi, const ExpertArgs& a, const PermBuffers
   GemmArgs g = gemm_args(epi, a, pb, pb.wide_off, max_tiles, H, O, part, lora);
   g.batch_off = pb.tile_off;
   g.skew = skew;
-  const dim3 grid = grouped_grid(max_tiles, g.n_tiles);
+  const dim3 grid = grouped_grid(max_tiles, g.n_tiles, tail_can_split(epi, (epi == 0 ? a.d : a.F) / BK));
   if (epi == 0) launch_grouped<0>(lora != nullptr, a.packed, grid, g, stream);
   else launch_grouped<1>(lora != nullptr, a.packed, grid, g, stream);
   return hipGetLastError();
@@ -929,7 +929,7 @@ hipError_t launch_experts_bf16(const ExpertArgs& a, const PermBuffers& pb, uint1
   }
   GemmArgs g = gemm_args(0, a, pb, pb.tile_off, max_tiles, H, O, part, lora);
   g.ab = ab;
-  launch_grouped<0>(lora != nullptr, a.packed, grouped_grid(max_tiles, g.n_tiles), g, stream);
+  launch_grouped<0>(lora != nullptr, a.packed, grouped_grid(max_tiles, g.n_tiles, tail_can_split(0, a.d / BK)), g, stream);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   record_mark(marks, 0, stream);
@@ -938,7 +938,7 @@ hipError_t launch_experts_bf16(const ExpertArgs& a, const PermBuffers& pb, uint1
     if (err != hipSuccess) return err;
   }
   g = gemm_args(1, a, pb, pb.tile_off, max_tiles, H, O, part, lora);
-  launch_grouped<1>(lora != nullptr, a.packed, grouped_grid(max_tiles, g.n_tiles), g, stream);
+  launch_grouped<1>(lora != nullptr, a.packed, grouped_grid(max_tiles, g.n_tiles, tail_can_split(1, a.F / BK)), g, stream);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   if (tail_can_split(1, a.F / BK)) {

@@ -27,8 +27,8 @@ CASES = [
     _cfg(65, 8, 2, 1, 256, 192),                                      # ... and one row more
     _cfg(120, 8, 2, 0, 128, 2048, L.ROUTE_SOFT_PRIOR, KEEP4),         # 64-row tiles, split reduction
     _cfg(121, 8, 2, 0, 128, 192, L.ROUTE_SOFT_PRIOR, KEEP4),
-    _cfg(144, 8, 2, 0, 128, 192, L.ROUTE_SOFT_PRIOR, KEEP4),
-    _cfg(145, 8, 2, 0, 128, 192, L.ROUTE_SOFT_PRIOR, KEEP4),
+    _cfg(144, 8, 2, 0, 128, 192, L.ROUTE_SOFT_PRIOR, KEEP4),          # the last batch of 64-row tiles
+    _cfg(145, 8, 2, 0, 128, 192, L.ROUTE_SOFT_PRIOR, KEEP4),          # 128-row tiles from here
     _cfg(128, 8, 2, 1, 320, 128),                                     # one tile exactly
     _cfg(129, 8, 2, 1, 128, 2048),                                    # one row more, split reduction
     _cfg(208, 8, 2, 0, 256, 256, L.ROUTE_HARD_MASK, KEEP4),           # the last batch, four experts
@@ -36,10 +36,10 @@ CASES = [
     _cfg(906, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),   # the last, many experts
     _cfg(597, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),
     _cfg(40, 256, 16, 8, 192, 64),                                    # the most experts and shared experts
-    # model widths (many chunks, several column tiles, a down reduction in slices): the last batch of
-    # 64-row tiles, the first of 128-row ones
+    # model widths (many chunks, several column tiles, a down reduction in slices): 64-row tiles, then the
+    # first batch of 128-row ones
     _cfg(128, 8, 2, 0, 1152, 2048),
-    _cfg(129, 8, 2, 1, 1152, 2048),
+    _cfg(145, 8, 2, 1, 1152, 2048),
     _cfg(100, 16, 2, 0, 1088, 2112, L.ROUTE_SOFT_PRIOR, KEEP4),
     # twelve experts take every token: more row tiles than the batch path keeps, so that the many-token
     # path's tiles run beside it

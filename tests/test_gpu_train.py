@@ -143,6 +143,7 @@ def _layer(cfg):
     (600, 320, 4096, 40, 2, 1, L.ROUTE_PLAIN, (), ()),
     (128, 1024, 4096, 8, 2, 0, L.ROUTE_PLAIN, (), (1, 4)),
     (129, 1024, 4096, 8, 2, 0, L.ROUTE_PLAIN, (), (1, 4)),
+    (150, 1024, 4096, 8, 2, 0, L.ROUTE_PLAIN, (), (1, 4)),
     (400, 1088, 2048, 8, 2, 0, L.ROUTE_PLAIN, (), (1, 4)),
     (256, 1024, 2048, 8, 1, 1, L.ROUTE_PLAIN, (), (3,)),
     (140, 512, 2048, 40, 6, 2, L.ROUTE_PLAIN, (), (3, 5, 11, 20, 21, 39)),
