@@ -11,15 +11,18 @@
 // and up values of a column meet in one lane.
 // Workgroups that share weight rows (a group's row tiles) are neighbours on one XCD and read them
 // through its L2; weights that one workgroup alone reads are loaded non-temporally.
-// Measured, Mixtral-shaped layer, packed, soft prior: 17 tokens 671 -> 437 us (gate/up 271 us =
-// 6.9 TB/s), 96 tokens 663 -> 480 us, 300 tokens 664 -> 605 us; DeepSeek-shaped, 333 tokens:
-// gate/up 189 -> 145 us, down 131 -> 83 us. Three or four chunks in flight changed nothing, and
+// Measured against the 256-row tiles, Mixtral-shaped layer, packed, soft prior: 17 tokens 668 -> 433 us
+// (gate/up 271 us = 6.9 TB/s), 96 tokens 664 -> 452, 200 tokens 675 -> 526; DeepSeek-shaped, 333 tokens:
+// 395 -> 267 (gate/up 189 -> 141, down 131 -> 78). Three or four chunks in flight changed nothing, and
 // 256 token rows (one workgroup per CU) lost 15-60%: its loads, LDS accesses and products no
 // longer overlap.
 // Adapted experts (LORA) take the adapters' term as one more chunk, as the many-token path does.
 // Every sum is formed in the many-token path's order, so that a layer gives the same bits on either
 // (and as its training forward): chunks in ascending order, and a down projection whose 256 x 256
-// tile that path would split (tile_slices) in the same slices, which batch_fixup_kernel adds in order.
+// tile that path would split (tile_slices) in the same slices, which batch_fixup_kernel adds in order
+// (5.6 us at 96 tokens). Starting neighbouring column tiles at different chunks, so that they do not read
+// the same columns at once, was 2 to 3% of a layer with row-major weights (none packed; 10% of the GEMMs at
+// d 2048, F 4096) and changed the bits: not done.
 
 #include "common.hpp"
 #include "gemm_tile.hpp"
@@ -366,19 +369,20 @@ hipError_t launch(int bm, bool packed, int grid, const BatchArgs& p, hipStream_t
 // By the rows an expert gets, since the time goes with the passes over the weights (row tiles).
 // Layer times with 64-row and 128-row tiles here and on the many-token path (256-row tiles whose
 // last one multiplies only its own 64-row pieces), by the average rows of a selectable expert:
-// Mixtral-shaped, plain routing, 24 rows 448 / 461 / 585 us, 75 rows 742 / 539 / 576, 100 rows
-// 705 / 574 / 585, 150 rows 957 / 955 / 625; hard mask over 4 experts, 75 rows 362 / 286 / 322,
-// 150 rows 485 / 488 / 339. A prior sends more rows to some experts, whose second 128-row tile is
-// another pass over their weights: `peak` is its largest entry over a uniform one's; soft prior
-// over 4 of 8 experts (peak 1.5), 50 rows 580 / 522 / 594, 75 rows 664 / 635 / 594. With dozens
-// of experts the tiles of neighbouring experts hide such passes and the line lies at the average:
-// DeepSeek-shaped, soft (peak 2.1), 31 rows 240 / 249 / 276, 66 rows 302 / 286 / 303, 94 rows
-// 360 / 329 / 317, 113 rows 396 / 354 / 328; over its 12-expert set, 32 rows 82 / 87 / 84, 100
-// rows 96 / 97 / 100, 200 rows 138 / 125 / 107.
+// Mixtral-shaped, plain routing, 24 rows 446 / 456 / 539 us, 75 rows 700 / 534 / 563, 100 rows
+// 708 / 579 / 574, 150 rows 917 / 888 / 612; hard mask over 4 experts, 75 rows 342 / 288 / 308,
+// 104 rows 361 / 311 / 314, 150 rows 471 / 447 / 332. A prior sends more rows to some experts, whose
+// second 128-row tile is another pass over their weights: `peak` is its largest entry over a uniform
+// one's; soft prior over 4 of 8 experts (peak 1.5), 36 rows 469 / 478 / 545, 50 rows 565 / 508 / 554, 71
+// rows 584 / 541 / 561. With dozens of experts the tiles of neighbouring experts hide such passes and the
+// line lies at the average: DeepSeek-shaped, soft (peak 2.1), 31 rows 247 / 255 / 281, 66 rows
+// 300 / 284 / 299, 84 rows 336 / 319 / 308, 113 rows 399 / 351 / 325; over its 12-expert set, 32 rows
+// 81 / 86 / 83, 100 rows 96 / 97 / 99, 200 rows 139 / 124 / 108. What the rows really are is known on the
+// device only (batch_skewed, below).
 int batch_tile_rows(int T, int K, int pool, float peak) {
   const double avg = static_cast<double>(T) * K / pool;
   if (avg <= 36) return 64;
-  return (pool >= 32 ? avg <= 85 : avg * peak <= 104) ? 128 : 0;
+  return (pool >= 32 ? avg <= 75 : avg * peak <= 104) ? 128 : 0;
 }
 
 hipError_t launch_experts_batch(const ExpertArgs& a, const PermBuffers& pb, int bm, int pool, uint16_t* H, uint16_t* O,

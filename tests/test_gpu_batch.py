@@ -33,7 +33,9 @@ CASES = [
     _cfg(129, 8, 2, 1, 128, 2048),                                    # one row more, split reduction
     _cfg(208, 8, 2, 0, 256, 256, L.ROUTE_HARD_MASK, KEEP4),           # the last batch, four experts
     _cfg(209, 8, 2, 0, 256, 256, L.ROUTE_HARD_MASK, KEEP4),           # the many-token path
-    _cfg(906, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),   # the last, many experts
+    _cfg(906, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),
+    _cfg(800, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),   # the last, many experts
+    _cfg(801, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),
     _cfg(597, 64, 6, 2, 128, 192, L.ROUTE_SOFT_PRIOR, tuple(synth.deepseek_mask_set())),
     _cfg(40, 256, 16, 8, 192, 64),                                    # the most experts and shared experts
     # model widths (many chunks, several column tiles, a down reduction in slices): 64-row tiles, then the
