@@ -328,6 +328,8 @@ int maskmoe_sample_mask(const float* mask_logits, const double* uniforms, int32_
  *  expert_out    device [T, K, d] float, required, 16-byte aligned: F_{A_t[k]}(x_t) as the
  *                combine used it (for bf16 layers: from the bf16-rounded SwiGLU activation,
  *                and itself rounded to bf16, as in y).
+ *  y             the bits of maskmoe_layer_forward on the same arguments: for f32 layers always,
+ *                for bf16 layers above 16 tokens (below, the few-token path sums in another order).
  *  workspace     at least maskmoe_layer_train_workspace_bytes(desc) bytes; for bf16 layers it
  *                keeps what maskmoe_layer_backward reads (the permutation, the SwiGLU
  *                activations and the gate / up pre-activations, bf16).
